@@ -298,7 +298,7 @@ int spconv_pack_lowered(int N, int C, int H, int W, const spconv_csr *csr, int K
 
 typedef struct spconv_plan_info {
     int32_t kernel;                /* SPCONV_KERNEL_STRIDE1, _GENERIC or _DENSE */
-    int32_t pixels_per_lane;       /* virtual output pixels per lane per image; dense: 32-pixel blocks per wave */
+    int32_t pixels_per_lane;       /* virtual output pixels per lane per image; dense: 32-pixel blocks per tile */
     int32_t images_per_group;      /* images sharing one workgroup's tile */
     int32_t channels_per_wave;     /* output channels (CSR rows) per wave; generic kernel: per workgroup */
     int32_t tile_rows;             /* output rows per spatial tile */
@@ -350,7 +350,7 @@ int spconv_plan(int N, int C, int H, int W, const spconv_csr *csr, int K, int R,
  *   SPCONV_KERNEL_STRIDE1_TILED  the same tuple, for the tilings built to run
  *                          several work items per workgroup
  *   SPCONV_KERNEL_GENERIC  (pixels_per_lane, 0, channels_per_workgroup, pool)
- *   SPCONV_KERNEL_DENSE    (R, S, pixel blocks per wave, pool)
+ *   SPCONV_KERNEL_DENSE    (R, S, pixel blocks per tile, pool)
  * with pool 0 or 1 and the other fields as spconv_plan_info reports them.
  * variants  host array of 4*capacity int32, nullable when capacity is 0; the
  *           first min(count, capacity) tuples are written.
@@ -363,7 +363,8 @@ int spconv_kernel_variants(int32_t kernel, int32_t *variants, int32_t capacity, 
 /*
  * Dense path. Above some density, skipping zeros no longer pays: the same
  * fused convolution computed with every filter tap on the matrix cores
- * (fp32 MFMA, so the arithmetic stays fp32 like the sparse path) is faster.
+ * (fp32 values as three bf16 parts each, fp32 sums: the error is that of the
+ * sparse path's fp32 arithmetic or less) is faster.
  * The paper reports that its sparse kernels beat the dense ones only below a
  * break-even density (Evaluation, sparse versus dense, on its CPUs); these
  * calls give the same choice on MI355X: spconv_select_path predicts which

@@ -5,22 +5,28 @@
 // The convolution is the implicit GEMM  out[k, p] = sum over (c, r, s) of
 // W[k, c, r, s] * Xp[c, p + r*Wp + s]  (stride 1, p = y*Wp + x, the paper's
 // offset trick with the padded row pitch as pixel pitch; columns x >= Wo are
-// computed and dropped). It runs in fp32 on v_mfma_f32_32x32x2f32, so products
-// and sums keep fp32 precision like the sparse path:
+// computed and dropped). Products are formed exactly enough for fp32: every
+// value is the sum of three bf16 parts, x = h + m + l (each the bf16 rounding
+// of what the parts before it leave, so the sum is exact), and a product takes
+// the six part products of weight 2^-16 or more, hh + hm + mh + mm + hl + lh,
+// on v_mfma_f32_32x32x16_bf16 with fp32 sums (what is dropped is below 2^-24
+// of the product). Six of them take 192 cycles for 16 channels, where the fp32
+// MFMA (32x32x2) takes 512.
 //  * a workgroup owns (image, tile of TH output rows, 32*nw output channels);
-//    each of its nw*ks waves owns 32 channels, NB blocks of 32 consecutive
-//    virtual pixels of the tile (one 32x32 accumulator tile per block) and
-//    every ks-th channel pair of the reduction; the ks partial sums of a tile
-//    are added through LDS in a fixed order at the end;
-//  * the tile's padded input rows are copied to LDS one channel chunk at a
-//    time with asynchronous global->LDS loads into two buffers;
-//  * the GEMM's reduction runs over channel pairs: one MFMA takes taps (2cp,
-//    t) and (2cp+1, t), so B is the staged input shifted by the tap offset —
-//    lanes 0-31 read 32 consecutive pixels of channel 2cp, lanes 32-63 of
-//    channel 2cp+1 — and A is one 256-byte load from the filter packed by
-//    spconv_pack_dense in exactly that fragment order;
+//    the tile's NB blocks of 32 consecutive virtual pixels are dealt to ksp
+//    waves per channel tile (NBW blocks each, one 32x32 accumulator tile per
+//    block) and the reduction's groups of 16 channels to ksr waves; the ksr
+//    partial sums of a tile are added through LDS in a fixed order at the end;
+//  * the tile's input rows are loaded one chunk of channel groups ahead into
+//    registers, split there and stored to LDS as [part][8-channel half][pixel]
+//    [8 bf16], so a B fragment (8 channels of a pixel shifted by the tap) is
+//    one 16-byte LDS read per part, consecutive over the lanes;
+//  * the A fragment of (group, tap) is four 8-byte loads from the filter
+//    packed by spconv_pack_dense, two steps ahead, split in registers;
 //  * the epilogue adds bias (and a residual), applies ReLU, pools 2x2 windows
-//    through a per-wave LDS tile when asked, and stores once.
+//    through LDS when asked, and stores once. An output that came out NaN is
+//    summed again in plain fp32: infinities (and values that round to one in
+//    bf16) have no finite parts.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -36,13 +42,21 @@ __attribute__((visibility("hidden"))) int dense_kernel_variants(int32_t *variant
 namespace {
 
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kDnsTile = dense_layout::kTile;  // MFMA tile: 32 channels x 32 pixels
-constexpr int kDnsMaxThreads = 512;       // nw * ks waves per workgroup, at most 8
-constexpr int kDnsMaxBlocks = 8;          // pixel blocks per wave (16 accumulator VGPRs each)
-constexpr int kDnsBlock = 256;            // floats per 16-byte-per-lane LDS DMA instruction
+constexpr int kDnsMaxThreads = 512;       // nw * ksr * ksp waves per workgroup, at most 8
+constexpr int kDnsMaxBlocks = 8;          // pixel blocks per tile
+constexpr int kDnsWaveBlocks = 4;         // pixel blocks per wave (16 accumulator VGPRs each)
+constexpr int kDnsGroup = 16;             // channels per MFMA (one reduction group)
+constexpr int kDnsPxBytes = 6 * kDnsGroup;  // LDS bytes of a group's pixel: three bf16 parts of 16 channels
 constexpr int kDnsLdsBytes = 64 * 1024;   // per workgroup: two resident per CU
+constexpr int kDnsLdsMax = 80 * 1024;     // one group of the widest rows (256 padded columns, 3 rows)
 constexpr int kDnsPoolCh = 8;             // channels of one pooled staging round (4 accumulator rows x 2 halves)
+constexpr int kDnsRounds = 3;             // staging tasks per thread whose loads run a chunk ahead
 
 struct DenseArgs {
     int N, C, K, Kp, Hp, Wp, Ho, Wo, Hq, Wq;
@@ -50,92 +64,136 @@ struct DenseArgs {
     int TH;          // output rows per tile
     int ntiles_y;    // tiles per image
     int nw;          // channel tiles of 32 per workgroup
-    int ks;          // waves splitting the reduction over channel pairs
+    int ksr;         // waves splitting the reduction over channel groups
+    int ksp;         // waves splitting the tile's pixel blocks
     int nkt;         // channel tiles of 32*nw
-    int Cc;          // channels per LDS chunk (even)
+    int Cg;          // channel groups per LDS chunk (a multiple of ksr)
     int nchunks;
-    int PLp;         // LDS floats per staged channel
-    // staging units dealt round-robin to the nw*ks waves: (channel, padded
-    // row) from an unpadded input, (channel, block of kDnsBlock) otherwise
-    UnitStep row_units, blk_units;
-    int buf_floats;  // Cc * PLp
-    size_t total_floats;  // N*C*Hp*Wp
+    int nbuf;        // LDS chunk buffers, 1 or 2
+    int PX;          // staged pixels per channel
+    int tasks;       // staging tasks of a chunk: (octet of channels, pixel), 2*Cg*PX
+    int buf_bytes;   // Cg * PX * kDnsPxBytes
     int total_wgs;
     int out_pad, opitch;
     size_t oplane;
     int res_pad, rpitch;
     size_t rplane;
     int wpk_bytes;   // bytes of the packed filter (below 2^31)
-    // epilogues: x / Wp, x / ((TH/2) * Wq) and x / Wq as multiply-shift
-    uint32_t wp_magic, pch_magic, wq_magic;
-    int wp_shift, pch_shift, wq_shift;
-    int unpadded;    // input is N x C x H x W: the border is formed in LDS
-    int H, W, pad, rows_in;
+    // x / PX (staging), x / Wp, and the pooled epilogue's x / ((TH/2) * Wq)
+    // and x / Wq as multiply-shift
+    uint32_t px_magic, wp_magic, pch_magic, wq_magic;
+    int px_shift, wp_shift, pch_shift, wq_shift;
+    // input planes: IH x IW with the tile's padded row i, column x at plane
+    // row i - ipad, column x - ipad (the padded tensor itself: ipad = 0)
+    int IH, IW, ipad;
 };
 
-// Queue the copy of one channel chunk of the tile: channel cl of the chunk gets
-// PLp floats from the tile's first padded row at buf + cl*PLp. A unit (channel,
-// block of 256 floats) is one 16-byte-per-lane copy; units are dealt round-
-// robin to the waves (the LDS-DMA engine's cost is per instruction, so 1 KiB
-// copies move four times the bytes of dword ones for the same cost); the last
-// block of a channel masks the lanes past PLp. Copies past the channel's rows
-// read the next rows (never used by a stored pixel); the buffer range stops
-// them at the end of the input tensor (such lanes read 0).
-__device__ __forceinline__ void dense_stage(const DenseArgs &a, const float *__restrict__ xp, float *buf, int ch,
-                                            int n, int row0, int wave, int lane) {
-    const int c0 = ch * a.Cc;
-    const int cn = min(a.Cc, a.C - c0);
-    const int plane = a.Hp * a.Wp;
-    const int nwaves = a.nw * a.ks;
-    if (a.unpadded) {
-        // Row by row from the unpadded input: padded row row0 + i is image row
-        // row0 + i - pad, written at column pad of the channel's LDS row i, 64
-        // floats per instruction (lanes past the row masked off). Border rows
-        // and columns keep the zeros stored before the first copy.
-        const int segs = (a.W + kWave - 1) / kWave;
-        int cl, i;
-        unit_first(a.row_units, wave, cl, i);
-        while (cl < cn) {
-            const int y = row0 + i - a.pad;
-            if (y >= 0 && y < a.H) {
-                const float *src = xp + (((size_t)n * a.C + c0 + cl) * a.H + y) * a.W;
-                float *dst = buf + cl * a.PLp + i * a.Wp + a.pad;
-                for (int sg = 0; sg < segs; ++sg) {
-                    const int x0 = sg * kWave;
-                    if (lane < a.W - x0)
-                        __builtin_amdgcn_global_load_lds((global_void_t *)(src + x0 + lane), (lds_void_t *)(dst + x0),
-                                                         4, 0, 0);
-                }
-            }
-            unit_next(a.row_units, cl, i);
-        }
-    }
-    if (!a.unpadded) {
-        const size_t first = ((size_t)n * a.C + c0) * plane + (size_t)row0 * a.Wp;
-        const size_t avail = (a.total_floats - first) * sizeof(float);
-        const int nrec = avail > 0xffffffffull ? (int)0xffffffffu : (int)(uint32_t)avail;
-        __amdgpu_buffer_rsrc_t rsrc =
-            __builtin_amdgcn_make_buffer_rsrc((void *)(xp + first), (short)0, nrec, 0x00020000);
-        int cl, b;
-        unit_first(a.blk_units, wave, cl, b);
-        while (cl < cn) {
-            // Byte offsets of a chunk fit 32 bits (the planner checks).
-            const uint32_t voff = (uint32_t)(cl * plane + b * kDnsBlock) * (uint32_t)sizeof(float) + lane * 16;
-            if (b * kDnsBlock + lane * 4 < a.PLp)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_t *)(buf + cl * a.PLp + b * kDnsBlock), 16,
-                                                         voff, 0, 0, 0);
-            unit_next(a.blk_units, cl, b);
-        }
-    }
-    // An odd last chunk reads one channel slot past the tensor's channels with
-    // zero weights; it must hold finite values: zero it.
-    if (cn & 1)
-        for (int e = (int)threadIdx.x; e < a.PLp; e += nwaves * kWave) buf[cn * a.PLp + e] = 0.0f;
+// bf16 parts of eight floats, two to a register (see the file comment).
+struct Parts {
+    u32x4_t h, m, l;
+};
+
+// Parts of floats 2*i and 2*i + 1; with r what the parts before leave.
+__device__ __forceinline__ void split2(Parts &p, int i, float x, float y) {
+    const f32x2_t v = {x, y};
+    const uint32_t hb = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+    const f32x2_t r1 = {x - __uint_as_float(hb << 16), y - __uint_as_float(hb & 0xffff0000u)};
+    const uint32_t mb = __builtin_bit_cast(uint32_t, __builtin_convertvector(r1, bf16x2_t));
+    const f32x2_t r2 = {r1.x - __uint_as_float(mb << 16), r1.y - __uint_as_float(mb & 0xffff0000u)};
+    p.h[i] = hb;
+    p.m[i] = mb;
+    p.l[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r2, bf16x2_t));
 }
 
-__device__ __forceinline__ void dense_wait_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// Buffer descriptor of a wave-uniform range. Parts of its address come from
+// divisions and 64-bit products, which run on the vector unit: without the way
+// back to scalars every load through it becomes a loop over the lanes'
+// descriptors.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const float *p, uint32_t bytes) {
+    const uint64_t u = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc((void *)(((uint64_t)hi << 32) | lo), (short)0,
+                                             (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
 
-template <int R, int S, int NB, bool POOL>
+// One staging task: eight channels of one staged pixel of a chunk.
+struct StageTask {
+    uint32_t voff;  // byte offset of the first channel's pixel from the chunk's first channel, or past its end
+    int lds;        // byte offset of the h part in the chunk buffer, or -1 (no task)
+};
+
+__device__ __forceinline__ StageTask dense_task(const DenseArgs &a, int id, int y0) {
+    StageTask t;
+    t.lds = -1;
+    t.voff = 0xfffffff0u;
+    if (id < a.tasks) {
+        const int oct = (int)fast_div((uint32_t)id, a.px_magic, a.px_shift);
+        const int px = id - oct * a.PX;
+        const int i = (int)fast_div((uint32_t)px, a.wp_magic, a.wp_shift);
+        const int y = y0 + i - a.ipad, x = px - i * a.Wp - a.ipad;
+        t.lds = (oct >> 1) * a.PX * kDnsPxBytes + ((oct & 1) * a.PX + px) * 16;
+        if (y >= 0 && y < a.IH && x >= 0 && x < a.IW)
+            t.voff = (uint32_t)((oct * 8 * a.IH + y) * a.IW + x) * (uint32_t)sizeof(float);
+    }
+    return t;
+}
+
+// The chunk's input through a descriptor over its channels of image n: border
+// pixels and channels past C read as zeros.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t dense_chunk_rsrc(const DenseArgs &a, const float *__restrict__ xp,
+                                                                   int ch, int n) {
+    const int c0 = ch * a.Cg * kDnsGroup;
+    const int cn = min(a.Cg * kDnsGroup, a.C - c0);
+    const size_t plane = (size_t)a.IH * a.IW;
+    return uniform_rsrc(xp + ((size_t)n * a.C + c0) * plane, (uint32_t)(cn * plane * sizeof(float)));
+}
+
+__device__ __forceinline__ void dense_load(const DenseArgs &a, const __amdgpu_buffer_rsrc_t &rsrc, const StageTask &t,
+                                           float (&v)[8]) {
+    const uint32_t pb = (uint32_t)(a.IH * a.IW) * (uint32_t)sizeof(float);
+    // A border pixel's offset stays past the range (no wrap): the step is 0 there.
+    const uint32_t step = t.voff == 0xfffffff0u ? 0u : pb;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        v[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, t.voff + j * step, 0, 0));
+}
+
+__device__ __forceinline__ void dense_put(const DenseArgs &a, char *buf, const StageTask &t, const float (&v)[8]) {
+    if (t.lds < 0) return;
+    Parts p;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) split2(p, i, v[2 * i], v[2 * i + 1]);
+    char *d = buf + t.lds;
+    *reinterpret_cast<u32x4_t *>(d) = p.h;
+    *reinterpret_cast<u32x4_t *>(d + a.PX * 32) = p.m;
+    *reinterpret_cast<u32x4_t *>(d + a.PX * 64) = p.l;
+}
+
+// Plain fp32 sum of one output, for results that came out NaN.
+template <int R, int S>
+__device__ __forceinline__ float dense_sum_fp32(const float *__restrict__ img, const float *__restrict__ wk,
+                                                          int C, int Kp, int IH, int IW, int y, int x) {
+    float s = 0.0f;
+    for (int c = 0; c < C; ++c)
+        for (int t = 0; t < R * S; ++t) {
+            const int yy = y + t / S, xx = x + t % S;
+            const float v = (yy >= 0 && yy < IH && xx >= 0 && xx < IW) ? img[((size_t)c * IH + yy) * IW + xx] : 0.0f;
+            s = fmaf(wk[((size_t)(c >> 1) * R * S + t) * Kp * 2 + (c & 1)], v, s);
+        }
+    return s;
+}
+
+// What bounds it: at 14x14 (256 channels, batch 32, one workgroup per CU) the
+// MFMAs alone take about 33 us (the chip holds 1.65 PFLOP/s on this MFMA form)
+// and everything else (the A loads and their split, LDS reads, staging) about
+// 35 us without them; together 54 us, where the fp32 MFMA kernel this replaces
+// took 88 us. Other layers, batch 32, before and after: 56x56, 64 channels 98
+// -> 68 us; 28x28, 128 channels, pooled 82 -> 51 us; 7x7, 512 channels 171 ->
+// 110 us; 112x112, 64 channels (batch 8) 97 -> 83 us. Against float64 the sums
+// are two to three times closer than that kernel's (14x14: 1.5e-7 against
+// 4.1e-7 relative), because the hh products round into the main sum once per
+// 16 channels and tap. Chunks of 32 to 96 channels take the same time.
+template <int R, int S, int NBW, bool POOL>
 __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs a, const float *__restrict__ xp,
                                                                             const float *__restrict__ wpk,
                                                                             const float *__restrict__ bias,
@@ -143,6 +201,7 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
                                                                             float *__restrict__ out) {
     extern __shared__ float lds[];
     constexpr int RS = R * S;
+    char *ldsb = reinterpret_cast<char *>(lds);
     const int lane = (int)threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int work = xcd_linear_id((int)blockIdx.x, a.total_wgs);
@@ -151,208 +210,329 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
     const int ty = rest % a.ntiles_y;
     const int n = rest / a.ntiles_y;
     const int y0 = ty * a.TH;
-    const int wn = wave % a.nw, wk = wave / a.nw;  // channel tile, reduction share
+    // channel tile, reduction share, pixel share
+    const int wn = __builtin_amdgcn_readfirstlane(wave % a.nw);
+    const int wr = __builtin_amdgcn_readfirstlane((wave / a.nw) % a.ksr);
+    const int wp = __builtin_amdgcn_readfirstlane(wave / (a.nw * a.ksr));
     const int k0 = (kt * a.nw + wn) * kDnsTile;
+    const int q0 = wp * NBW * kDnsTile;  // first virtual pixel of the wave
     const int half = lane >> 5, col = lane & 31;
+    const int nthreads = (int)blockDim.x;
+    // A wave whose blocks hold no stored pixel computes nothing.
+    const bool active = q0 < (min(a.TH, a.Ho - y0) - 1) * a.Wp + a.Wo;
 
-    // CH independent accumulator chains per pixel block: with one block a
-    // wave's MFMAs would form one dependent chain, so its taps alternate
-    // between two accumulators, added once after the loop.
-    constexpr int CH = NB == 1 ? 2 : 1;
-    f32x16_t acc[NB * CH];
+    // Sums of the hh products, and of the five smaller ones: added once at the
+    // end, so that the main sum rounds once per 16 channels and tap.
+    f32x16_t acc[NBW], low[NBW];
 #pragma unroll
-    for (int b = 0; b < NB * CH; ++b)
+    for (int b = 0; b < NBW; ++b)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[b][r] = 0.0f;
+        for (int r = 0; r < 16; ++r) acc[b][r] = low[b][r] = 0.0f;
 
-    // A fragment of (pair cp, tap t): wpk[((cp*RS + t)*Kp + k0 + col)*2 + half],
-    // read through a buffer descriptor: the lane's part is a fixed VGPR
-    // offset, the (pair, tap) part one scalar offset.
-    const __amdgpu_buffer_rsrc_t wrs =
-        __builtin_amdgcn_make_buffer_rsrc((void *)wpk, (short)0, a.wpk_bytes, 0x00020000);
-    const int wvoff = ((k0 + col) * 2 + half) * (int)sizeof(float);
-    const int wtap_bytes = a.Kp * 2 * (int)sizeof(float);
-    // B fragment: the staged channel 2cp + half, pixel 32*b + col, shifted by r*Wp + s.
-    const int lane_b = half * a.PLp + col;
+    // A fragment of (group g, tap t), channel pair j of the lane's half:
+    // wpk[(((8g + 4*half + j)*RS + t)*Kp + k0 + col)*2 ..]. The descriptor
+    // starts at the group and the lane's offset counts its pair, so pairs past
+    // the filter (C not a multiple of 16, or a group past the last) read zeros
+    // whatever the scalar tap offset.
+    const int npairs = (a.C + 1) / 2;
+    const uint32_t wtap = (uint32_t)a.Kp * 8u, wpair = wtap * RS;
+    uint32_t wlane[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) wlane[j] = (uint32_t)(k0 + col) * 8u + (uint32_t)(4 * half + j) * wpair;
+    auto a_rsrc = [&](int g) {
+        const int left = max(npairs - 8 * g, 0);
+        return uniform_rsrc(wpk + (size_t)(left ? 8 * g : 0) * (wpair / 4), (uint32_t)min(left, 8) * wpair);
+    };
+    auto load_a = [&](f32x2_t(&av)[4], const __amdgpu_buffer_rsrc_t &rs, int t) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            av[j] = __builtin_bit_cast(f32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rs, wlane[j], t * wtap, 0));
+    };
 
-    if (a.unpadded) {
-        for (int e = (int)threadIdx.x * 4; e < 2 * a.buf_floats; e += (int)blockDim.x * 4)
-            *reinterpret_cast<float4 *>(lds + e) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        __syncthreads();
+    StageTask task[kDnsRounds];
+    float xin[kDnsRounds][8];
+#pragma unroll
+    for (int i = 0; i < kDnsRounds; ++i) task[i] = dense_task(a, (int)threadIdx.x + i * nthreads, y0);
+    auto stage_load = [&](int ch) {
+        const __amdgpu_buffer_rsrc_t rsrc = dense_chunk_rsrc(a, xp, ch, n);
+#pragma unroll
+        for (int i = 0; i < kDnsRounds; ++i)
+            if (i * nthreads < a.tasks) dense_load(a, rsrc, task[i], xin[i]);
+    };
+    // Split and store the loaded chunk, and the tasks past the rounds kept in registers.
+    auto stage_put = [&](int ch, char *buf) {
+#pragma unroll
+        for (int i = 0; i < kDnsRounds; ++i)
+            if (i * nthreads < a.tasks) dense_put(a, buf, task[i], xin[i]);
+        if (kDnsRounds * nthreads < a.tasks) {
+            const __amdgpu_buffer_rsrc_t rsrc = dense_chunk_rsrc(a, xp, ch, n);
+            for (int id = (int)threadIdx.x + kDnsRounds * nthreads; id < a.tasks; id += kDnsRounds * nthreads) {
+                StageTask t[kDnsRounds];
+                float v[kDnsRounds][8];
+#pragma unroll
+                for (int i = 0; i < kDnsRounds; ++i) {
+                    t[i] = dense_task(a, id + i * nthreads, y0);
+                    dense_load(a, rsrc, t[i], v[i]);
+                }
+#pragma unroll
+                for (int i = 0; i < kDnsRounds; ++i) dense_put(a, buf, t[i], v[i]);
+            }
+        }
+    };
+
+    stage_load(0);
+    const int ngroups = (a.C + kDnsGroup - 1) / kDnsGroup;
+    const int lane_b = (half * a.PX + q0 + col) * 16;
+    // Steps of this wave: (group, tap), groups wr, wr + ksr, ... over all
+    // chunks. A wave runs them as one pipeline: the A loads three steps ahead,
+    // the split of the next step's A and the B reads of the next unit (one
+    // block of a step) between the six MFMAs of the current unit.
+    f32x2_t araw[3][4];
+    Parts A;
+    if (active) {
+        load_a(araw[0], a_rsrc(wr), 0);
+        load_a(araw[1], a_rsrc(wr + 1 / RS * a.ksr), 1 % RS);
+        load_a(araw[2], a_rsrc(wr + 2 / RS * a.ksr), 2 % RS);
     }
-    dense_stage(a, xp, lds, 0, n, y0, wave, lane);
-    dense_wait_copies();
+    stage_put(0, ldsb);
+    if (active)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) split2(A, j, araw[0][j].x, araw[0][j].y);
     __syncthreads();
 
-    // Two A register sets alternate over this wave's pairs (wk, wk + ks, ...)
-    // of each chunk: the loads for the next pair are in flight while the MFMAs
-    // of the current one issue. With few blocks a pair's MFMAs are short next
-    // to an A load's latency (an L2 hit), and a third set keeps two pairs'
-    // loads in flight.
-    constexpr bool kA3 = NB <= 4;
-    auto mma_pair = [&](const float(&av)[RS], int cp, const float *bb) {
-        const float *bp = bb + 2 * cp * a.PLp;
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int s = 0; s < S; ++s) {
-                const float *bt = bp + r * a.Wp + s;
-                const int chain = CH == 2 ? ((r * S + s) & 1) : 0;
-#pragma unroll
-                for (int b = 0; b < NB; ++b)
-                    acc[b * CH + chain] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[r * S + s], bt[kDnsTile * b],
-                                                                             acc[b * CH + chain], 0, 0, 0);
-            }
+    // The wave's last block may lie past the stored pixels: it then reads the
+    // first block's pixels again (its sums are dropped).
+    const int valid_px = (a.TH - 1) * a.Wp + a.Wo;
+    const int last_off = q0 + (NBW - 1) * kDnsTile < valid_px ? (NBW - 1) * kDnsTile * 16 : 0;
+    auto read_b = [&](Parts &u, const char *bp, int b) {
+        const char *bb = bp + (NBW > 1 && b == NBW - 1 ? last_off : b * kDnsTile * 16);
+        u.h = *reinterpret_cast<const u32x4_t *>(bb);
+        u.m = *reinterpret_cast<const u32x4_t *>(bb + a.PX * 32);
+        u.l = *reinterpret_cast<const u32x4_t *>(bb + a.PX * 64);
     };
-    auto load_a = [&](float(&av)[RS], int gcp) {
-        const int base = gcp * RS * wtap_bytes;
-#pragma unroll
-        for (int t = 0; t < RS; ++t)
-            av[t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wrs, wvoff, base + t * wtap_bytes, 0));
+    auto mma = [&](f32x16_t &c, const u32x4_t &x, const u32x4_t &y) {
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, x), __builtin_bit_cast(bf16x8_t, y), c,
+                                                    0, 0, 0);
     };
+
     for (int ch = 0; ch < a.nchunks; ++ch) {
-        if (ch + 1 < a.nchunks) dense_stage(a, xp, lds + ((ch + 1) & 1) * a.buf_floats, ch + 1, n, y0, wave, lane);
-        const float *bb = lds + (ch & 1) * a.buf_floats + lane_b;
-        const int c0 = ch * a.Cc;
-        const int npairs = (min(a.Cc, a.C - c0) + 1) / 2;
-        const int gcp0 = c0 / 2;
-        if constexpr (kA3) {
-            // Three A sets: the loads of the next two pairs are in flight.
-            float a0[RS], a1[RS], a2[RS];
-            const int st = a.ks;
-            if (wk < npairs) load_a(a0, gcp0 + wk);
-            if (wk + st < npairs) load_a(a1, gcp0 + wk + st);
-            for (int cp = wk; cp < npairs; cp += 3 * st) {
-                if (cp + 2 * st < npairs) load_a(a2, gcp0 + cp + 2 * st);
-                mma_pair(a0, cp, bb);
-                if (cp + st >= npairs) break;
-                if (cp + 3 * st < npairs) load_a(a0, gcp0 + cp + 3 * st);
-                mma_pair(a1, cp + st, bb);
-                if (cp + 2 * st >= npairs) break;
-                if (cp + 4 * st < npairs) load_a(a1, gcp0 + cp + 4 * st);
-                mma_pair(a2, cp + 2 * st, bb);
-            }
-        } else {
-            float a0[RS], a1[RS];
-            if (wk < npairs) load_a(a0, gcp0 + wk);
-            for (int cp = wk; cp < npairs; cp += 2 * a.ks) {
-                const int cq = cp + a.ks;
-                if (cq < npairs) load_a(a1, gcp0 + cq);
-                mma_pair(a0, cp, bb);
-                if (cq < npairs) {
-                    if (cq + a.ks < npairs) load_a(a0, gcp0 + cq + a.ks);
-                    mma_pair(a1, cq, bb);
+        const bool more = ch + 1 < a.nchunks;
+        if (more) stage_load(ch + 1);
+        const char *buf = ldsb + (a.nbuf == 2 ? (ch & 1) * a.buf_bytes : 0) + lane_b;
+        const int gn = min(a.Cg, ngroups - ch * a.Cg);
+        const int gstride = a.PX * kDnsPxBytes;
+        if (active && wr < gn) {
+            Parts B[2];
+            read_b(B[0], buf + wr * gstride, 0);
+            for (int g = wr; g < gn; g += a.ksr) {
+                const char *gb = buf + g * gstride;
+                const char *gnext = g + a.ksr < gn ? gb + a.ksr * gstride : gb;  // (the last group's reads repeat)
+                const int gg = ch * a.Cg + g;
+                const __amdgpu_buffer_rsrc_t rs0 = a_rsrc(gg), rs1 = a_rsrc(gg + (RS == 1 ? 3 : 1) * a.ksr);
+#pragma unroll
+                for (int t = 0; t < RS; ++t) {
+                    // araw[t % 3] is split already: its registers take step t + 3.
+                    load_a(araw[t % 3], t + 3 < RS ? rs0 : rs1, (t + 3) % RS);
+                    Parts An;
+#pragma unroll
+                    for (int b = 0; b < NBW; ++b) {
+                        const int un = t * NBW + b, tn = (un + 1) / NBW, bn = (un + 1) % NBW;
+                        read_b(B[(un + 1) & 1], tn < RS ? gb + ((tn / S) * a.Wp + tn % S) * 16 : gnext, bn);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (j * NBW / 4 == b) {  // the split's four pairs, dealt to the units
+                                split2(An, j, araw[(t + 1) % 3][j].x, araw[(t + 1) % 3][j].y);
+                                // (kept in this unit: the compiler would sink it to the next step's first use)
+                                asm volatile("" : "+v"(An.h[j]), "+v"(An.m[j]), "+v"(An.l[j]));
+                            }
+                        const Parts &Bu = B[un & 1];
+                        mma(low[b], A.l, Bu.h);
+                        mma(low[b], A.h, Bu.l);
+                        mma(low[b], A.m, Bu.m);
+                        mma(low[b], A.m, Bu.h);
+                        mma(low[b], A.h, Bu.m);
+                        mma(acc[b], A.h, Bu.h);
+                        if constexpr (RS > 1) {
+                            __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);              // LDS reads
+                            if (b == 0) __builtin_amdgcn_sched_group_barrier(0x020, 4, 0);  // A loads
+#pragma unroll
+                            for (int k = 0; k < 6; ++k) {
+                                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+                                __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);  // VALU
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                    A = An;
+                }
+                if constexpr ((RS * NBW) % 2 == 1) B[0] = B[1];
+                if constexpr (RS % 3 != 0) {  // one tap: the ring turns by copies
+                    static_assert(RS == 1, "filters of the dense kernel");
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const f32x2_t v = araw[0][j];
+                        araw[0][j] = araw[1][j];
+                        araw[1][j] = araw[2][j];
+                        araw[2][j] = v;
+                    }
                 }
             }
         }
-        dense_wait_copies();
+        if (more) {
+            if (a.nbuf == 1) __syncthreads();
+            stage_put(ch + 1, ldsb + (a.nbuf == 2 ? ((ch + 1) & 1) * a.buf_bytes : 0));
+            __syncthreads();
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < NBW; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[b][r] += low[b][r];
+
+    // Sum the ksr partial tiles, in order 0, 1, ..., through LDS; wave wr keeps
+    // accumulator registers wr*J .. wr*J + J - 1 (fin[b][jj], J = 16 / ksr), so
+    // every wave has a share of the epilogue.
+    const int J = 16 / a.ksr, j0 = wr * J;
+    if (a.ksr > 1) {
+        __syncthreads();  // the chunk buffers are free
+        float *red = lds + (size_t)(wp * a.nw + wn) * a.ksr * NBW * 16 * kWave + lane;
+#pragma unroll
+        for (int b = 0; b < NBW; ++b)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) red[((wr * NBW + b) * 16 + j) * kWave] = acc[b][j];
         __syncthreads();
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) {
+            if (jj >= J) break;
+#pragma unroll
+            for (int b = 0; b < NBW; ++b) {
+                float s = red[(b * 16 + j0 + jj) * kWave];
+                for (int k = 1; k < a.ksr; ++k) s += red[((k * NBW + b) * 16 + j0 + jj) * kWave];
+                acc[b][jj] = s;
+            }
+        }
     }
 
-    if constexpr (CH == 2)
+    // acc[b][jj] is channel chan(jj) at virtual pixel q0 + 32*b + col of the
+    // tile. Row and column of the lane's pixel in each block (-1: not stored).
+    auto chan = [&](int jj) {
+        const int j = j0 + jj;
+        return k0 + 8 * (j >> 2) + 4 * half + (j & 3);
+    };
+    int ys[NBW], xs[NBW];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[0][r] += acc[1][r];
-
-    // Sum the ks partial tiles into the waves with wk == 0, in order wk = 1,
-    // 2, ...; the chunk buffers are free after the loop's last barrier.
-    if (a.ks > 1) {
-        float *red = lds + (size_t)wn * NB * 16 * kWave;
-        for (int k = 1; k < a.ks; ++k) {
-            if (wk == k)
+    for (int b = 0; b < NBW; ++b) {
+        const int q = q0 + kDnsTile * b + col;
+        const int yl = (int)fast_div((uint32_t)q, a.wp_magic, a.wp_shift), x = q - yl * a.Wp;
+        const bool in = yl < a.TH && x < a.Wo && y0 + yl < a.Ho;
+        ys[b] = in ? y0 + yl : -1;
+        xs[b] = x;
+    }
+    // NaN sums of stored outputs are taken again in fp32 (see the file comment).
+    uint64_t redo = 0;
 #pragma unroll
-                for (int b = 0; b < NB; ++b)
+    for (int b = 0; b < NBW; ++b)
 #pragma unroll
-                    for (int j = 0; j < 16; ++j) red[(b * 16 + j) * kWave + lane] = acc[b][j];
-            __syncthreads();
-            if (wk == 0)
+        for (int jj = 0; jj < 16; ++jj)
+            if (jj < J && ys[b] >= 0 && chan(jj) < a.K && acc[b][jj] != acc[b][jj]) redo |= 1ull << (b * 16 + jj);
+    if (__builtin_amdgcn_ballot_w64(redo != 0)) {
+        const float *img = xp + (size_t)n * a.C * a.IH * a.IW;
+        while (redo) {
+            const int e = __builtin_ctzll(redo);
+            redo &= redo - 1;
+            int y = 0, x = 0;
 #pragma unroll
-                for (int b = 0; b < NB; ++b)
+            for (int b = 0; b < NBW; ++b)
+                if (b == e >> 4) {
+                    y = ys[b];
+                    x = xs[b];
+                }
+            const float s = dense_sum_fp32<R, S>(img, wpk + (size_t)chan(e & 15) * 2, a.C, a.Kp, a.IH, a.IW,
+                                                 y - a.ipad, x - a.ipad);
 #pragma unroll
-                    for (int j = 0; j < 16; ++j) acc[b][j] += red[(b * 16 + j) * kWave + lane];
-            __syncthreads();
+            for (int b = 0; b < NBW; ++b)
+#pragma unroll
+                for (int jj = 0; jj < 16; ++jj)
+                    if (e == b * 16 + jj) acc[b][jj] = s;
         }
-        if (wk != 0) return;
     }
 
-    // Accumulator (block b, register j) holds channel k0 + 8*(j/4) + 4*half + j%4
-    // at virtual pixel 32*b + col of the tile.
-    const int tile_px = a.TH * a.Wp;
-    const bool stream = a.out_pad == 0;
-    if constexpr (!POOL) {
-        // Row and column of this lane's pixel in each block (-1: not stored).
-        int ys[NB], xs[NB];
+    // Bias, residual and ReLU of registers 4*gq .. 4*gq + 3 (the residuals of
+    // all blocks are loaded before the first is used).
+    auto finish4 = [&](int gq) {
+        float rv[4][NBW], bk[4];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int q = kDnsTile * b + col;
-            const int yl = (int)fast_div((uint32_t)q, a.wp_magic, a.wp_shift), x = q - yl * a.Wp;
-            const bool in = q < tile_px && x < a.Wo && y0 + yl < a.Ho;
-            ys[b] = in ? y0 + yl : -1;
-            xs[b] = x;
+        for (int u = 0; u < 4; ++u) {
+            const int k = chan(4 * gq + u);
+            bk[u] = (bias && k < a.K) ? bias[k] : 0.0f;
+            if (res) {
+                const float *rplane = res + ((size_t)n * a.K + k) * a.rplane + a.res_pad * (a.rpitch + 1);
+#pragma unroll
+                for (int b = 0; b < NBW; ++b)
+                    rv[u][b] = (ys[b] >= 0 && k < a.K) ? rplane[(size_t)ys[b] * a.rpitch + xs[b]] : 0.0f;
+            }
         }
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int k = k0 + 8 * (j >> 2) + 4 * half + (j & 3);
-            if (k >= a.K) continue;
-            const float bk = bias ? bias[k] : 0.0f;
-            float *plane = out + ((size_t)n * a.K + k) * a.oplane;
-            const float *rplane = res ? res + ((size_t)n * a.K + k) * a.rplane : nullptr;
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int y = ys[b], x = xs[b];
-                if (y < 0) continue;
-                float v = acc[b][j] + bk;
-                if (rplane) v += rplane[(size_t)(y + a.res_pad) * a.rpitch + x + a.res_pad];
+            for (int b = 0; b < NBW; ++b) {
+                float v = acc[b][4 * gq + u] + bk[u];
+                if (res) v += rv[u][b];
                 if (a.relu) v = v > 0.0f ? v : 0.0f;
-                store_out(plane + (size_t)(y + a.out_pad) * a.opitch + x + a.out_pad, v, stream);
+                acc[b][4 * gq + u] = v;
+            }
+    };
+    const bool stream = a.out_pad == 0;
+    const int share = wr * a.ksp + wp, shares = a.ksr * a.ksp;  // this wave among its channel tile's
+    if constexpr (!POOL) {
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq) {
+            if (4 * gq >= J) break;
+            finish4(gq);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int k = chan(4 * gq + u);
+                if (k >= a.K) continue;
+                float *plane = out + ((size_t)n * a.K + k) * a.oplane + a.out_pad * (a.opitch + 1);
+#pragma unroll
+                for (int b = 0; b < NBW; ++b)
+                    if (ys[b] >= 0) store_out(plane + (size_t)ys[b] * a.opitch + xs[b], acc[b][4 * gq + u], stream);
             }
         }
         if (a.out_pad) {
             const int r1 = min(y0 + a.TH, a.Ho);
-            for (int kk = k0; kk < min(k0 + kDnsTile, a.K); ++kk)
+            for (int kk = k0 + share; kk < min(k0 + kDnsTile, a.K); kk += shares)
                 zero_border(out + ((size_t)n * a.K + kk) * a.oplane, y0, r1, a.Ho, a.Wo, a.out_pad, a.opitch, ty == 0,
                             ty == a.ntiles_y - 1, lane, kWave);
         }
     } else {
-        // Pool through a per-wave LDS tile, 8 channels at a time: activated
-        // values on the conv grid, then the max of each 2x2 window. Only this
-        // wave touches its area, and its LDS operations execute in issue
-        // order; the chunk loop's last barrier ordered these writes after
-        // every wave's reads of the input buffers.
-        constexpr int kPx = NB * kDnsTile;
-        float *st = lds + wn * kDnsPoolCh * kPx;
+        // Pool through LDS, 8 channels of each (channel tile, reduction share)
+        // at a time: its ksp waves stage the activated values of their blocks,
+        // then take the max of each 2x2 window between them.
+        const int px = a.ksp * NBW * kDnsTile;
+        float *st = lds + (size_t)(wn * a.ksr + wr) * kDnsPoolCh * px;
         const int prow0 = y0 / 2;
         const int prows = a.TH / 2;
         const int per_ch = prows * a.Wq;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
+        for (int gq = 0; gq < 4; ++gq) {
+            if (4 * gq >= J) break;
+            finish4(gq);
+            __syncthreads();  // the chunk buffers, or the previous round's values, are read
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                const int j = 4 * g + jj;
-                const int k = k0 + 8 * g + 4 * half + jj;
-                const float bk = (bias && k < a.K) ? bias[k] : 0.0f;
-                const float *rplane = (res && k < a.K) ? res + ((size_t)n * a.K + k) * a.rplane : nullptr;
+            for (int u = 0; u < 4; ++u)
 #pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    const int q = kDnsTile * b + col;
-                    float v = acc[b][j] + bk;
-                    if (rplane) {
-                        const int yl = (int)fast_div((uint32_t)q, a.wp_magic, a.wp_shift), x = q - yl * a.Wp;
-                        if (q < tile_px && x < a.Wo && y0 + yl < a.Ho)
-                            v += rplane[(size_t)(y0 + yl + a.res_pad) * a.rpitch + x + a.res_pad];
-                    }
-                    if (a.relu) v = v > 0.0f ? v : 0.0f;
-                    st[(4 * half + jj) * kPx + q] = v;
-                }
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            for (int t = lane; t < kDnsPoolCh * per_ch; t += kWave) {
+                for (int b = 0; b < NBW; ++b)
+                    st[(4 * half + u) * px + q0 + kDnsTile * b + col] = acc[b][4 * gq + u];
+            __syncthreads();
+            for (int t = wp * kWave + lane; t < kDnsPoolCh * per_ch; t += a.ksp * kWave) {
                 const int cc = (int)fast_div((uint32_t)t, a.pch_magic, a.pch_shift);
                 const int rem = t - cc * per_ch;
                 const int r = (int)fast_div((uint32_t)rem, a.wq_magic, a.wq_shift), jq = rem - r * a.Wq;
-                const int k = k0 + 8 * g + cc;
+                const int k = k0 + 8 * ((j0 >> 2) + gq) + cc;
                 const int pr = prow0 + r;
                 if (k < a.K && pr < a.Hq) {
-                    const float *s0 = st + cc * kPx + 2 * r * a.Wp + 2 * jq;
+                    const float *s0 = st + cc * px + 2 * r * a.Wp + 2 * jq;
                     const float m = fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[a.Wp], s0[a.Wp + 1]));
                     store_out(out + ((size_t)n * a.K + k) * a.oplane + (size_t)(pr + a.out_pad) * a.opitch + jq +
                                   a.out_pad,
@@ -362,7 +542,7 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
         }
         if (a.out_pad) {
             const int r1 = min(prow0 + prows, a.Hq);
-            for (int kk = k0; kk < min(k0 + kDnsTile, a.K); ++kk)
+            for (int kk = k0 + share; kk < min(k0 + kDnsTile, a.K); kk += shares)
                 zero_border(out + ((size_t)n * a.K + kk) * a.oplane, prow0, r1, a.Hq, a.Wq, a.out_pad, a.opitch,
                             ty == 0, ty == a.ntiles_y - 1, lane, kWave);
         }
@@ -371,43 +551,40 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
 
 using DenseKernel = void (*)(DenseArgs, const float *, const float *, const float *, const float *, float *);
 
-template <int R, int S, int NB>
+template <int R, int S, int NBW>
 DenseKernel pick_dense_pool(bool pool) {
-    return pool ? spconv_dense_kernel<R, S, NB, true> : spconv_dense_kernel<R, S, NB, false>;
+    return pool ? spconv_dense_kernel<R, S, NBW, true> : spconv_dense_kernel<R, S, NBW, false>;
 }
 
 template <int R, int S>
-DenseKernel pick_dense_nb(int NB, bool pool) {
-    switch (NB) {
+DenseKernel pick_dense_nbw(int NBW, bool pool) {
+    switch (NBW) {
         case 1: return pick_dense_pool<R, S, 1>(pool);
         case 2: return pick_dense_pool<R, S, 2>(pool);
         case 3: return pick_dense_pool<R, S, 3>(pool);
-        case 4: return pick_dense_pool<R, S, 4>(pool);
-        case 5: return pick_dense_pool<R, S, 5>(pool);
-        case 6: return pick_dense_pool<R, S, 6>(pool);
-        case 7: return pick_dense_pool<R, S, 7>(pool);
-        case 8: return pick_dense_pool<R, S, kDnsMaxBlocks>(pool);
+        case 4: return pick_dense_pool<R, S, kDnsWaveBlocks>(pool);
         default: return nullptr;
     }
 }
 
 // Filter shapes the dense kernel is built for.
-DenseKernel pick_dense(int R, int S, int NB, bool pool) {
-    if (R == 3 && S == 3) return pick_dense_nb<3, 3>(NB, pool);
-    if (R == 1 && S == 1) return pick_dense_nb<1, 1>(NB, pool);
+DenseKernel pick_dense(int R, int S, int NBW, bool pool) {
+    if (R == 3 && S == 3) return pick_dense_nbw<3, 3>(NBW, pool);
+    if (R == 1 && S == 1) return pick_dense_nbw<1, 1>(NBW, pool);
     return nullptr;
 }
 
 }  // namespace
 
-// (R, S, blocks per wave, pool) of every compiled dense instance (a library-
-// internal helper of spconv_kernel_variants, not exported).
+// (R, S, blocks per tile, pool) of every tile shape of the dense kernel (a
+// library-internal helper of spconv_kernel_variants, not exported). Tiles of
+// more than one block share them between waves, so several tile shapes run one
+// compiled instance.
 __attribute__((visibility("hidden"))) int dense_kernel_variants(int32_t *variants, int32_t capacity, int32_t *count) {
     int n = 0;
     for (int rs : {3, 1})
         for (int nb = 1; nb <= kDnsMaxBlocks; ++nb)
-            for (int pool = 0; pool < 2; ++pool)
-                if (pick_dense(rs, rs, nb, pool != 0)) {
+            for (int pool = 0; pool < 2; ++pool) {
                     if (n < capacity) {
                         variants[4 * n] = rs;
                         variants[4 * n + 1] = rs;
@@ -423,7 +600,8 @@ __attribute__((visibility("hidden"))) int dense_kernel_variants(int32_t *variant
 namespace {
 
 struct DensePlan {
-    int TH = 0, ntiles_y = 0, NB = 0, nw = 0, ks = 1, nkt = 0, Cc = 0, nchunks = 0, PLp = 0, total_wgs = 0;
+    int TH = 0, ntiles_y = 0, NB = 0, NBW = 0, nw = 0, ksr = 1, ksp = 1, nkt = 0, Cg = 0, nchunks = 0, nbuf = 1;
+    int PX = 0, total_wgs = 0;
     size_t lds_bytes = 0;
 };
 
@@ -434,28 +612,64 @@ int dense_waves(int K) { return dense_layout::waves(K); }
 // Kp of the packed filter: K rounded up to whole workgroup channel tiles.
 int dense_kp(int K) { return dense_layout::kp(K); }
 
-// Waves that split the reduction over channel pairs (1, 2 or 4), each adding
-// a 32-channel partial tile that is summed through LDS: 2 where the workgroup
-// (8 waves), the LDS area of the partial tiles (64 KiB) and the chunk's pairs
-// allow, 4 only when even 2 would leave the grid under 1024 waves (measured:
-// 4 splits cost up to 30% more than 2 on grids that have enough waves).
-int dense_ks(long long base_waves, int nw, int NB, int Cc) {
-    const size_t red_bytes = (size_t)nw * NB * 16 * kWave * sizeof(float);
-    int ks = 1;
-    auto fits = [&](int k) { return nw * k * kWave <= kDnsMaxThreads && red_bytes <= (size_t)kDnsLdsBytes && k <= Cc / 2; };
-    if (fits(2)) ks = 2;
-    if (ks == 2 && base_waves * 2 < 1024 && fits(4)) ks = 4;
-    return ks;
+// Waves per channel tile (1, 2 or 4): two where the workgroup has room, four
+// only when even two would leave the grid under 1024 waves.
+int dense_split(long long base_waves, int nw) {
+    int ws = nw * 2 * kWave <= kDnsMaxThreads ? 2 : 1;
+    if (ws == 2 && base_waves * 2 < 1024 && nw * 4 * kWave <= kDnsMaxThreads) ws = 4;
+    return ws;
+}
+
+// Splits a tile's waves and LDS. The ws waves of a channel tile share its pixel
+// blocks until each has at most four (accumulators; with three or four an A
+// fragment's split and loads are small next to its MFMAs), and the reduction
+// from there on; where the partial tiles or a chunk of that many groups do not
+// fit the LDS they share pixels only. A chunk holds as many channel groups as
+// threads can load ahead (kDnsRounds tasks each), in two buffers where they fit.
+bool dense_layout_tile(int C, int Wp, int Wo, int R, int S, bool pool, int ws, DensePlan *q) {
+    const int valid = (q->TH - 1) * Wp + Wo;  // virtual pixels up to the last stored one
+    const int nbv = (valid + kDnsTile - 1) / kDnsTile;
+    const int ngroups = (C + kDnsGroup - 1) / kDnsGroup;
+    q->PX = valid + (R - 1) * Wp + S - 1;
+    const long long unit = (long long)q->PX * kDnsPxBytes;
+    for (int ksr = ws; ksr >= 1; ksr /= 2) {
+        const int ksp = ws / ksr;
+        const int nbw = (nbv + ksp - 1) / ksp;
+        if (nbw > kDnsWaveBlocks || ksr > ngroups) continue;
+        // Lanes of the last block past the stored pixels read on past PX.
+        const int slack = std::max(0, nbv * kDnsTile + (R - 1) * Wp + S - 1 - q->PX) * 16;
+        size_t epi = pool ? (size_t)q->nw * ksr * kDnsPoolCh * ksp * nbw * kDnsTile * sizeof(float) : 0;
+        if (ksr > 1) epi = std::max(epi, (size_t)q->nw * ws * nbw * 16 * kWave * sizeof(float));
+        if (epi > (size_t)kDnsLdsBytes) continue;
+        const int threads = q->nw * ws * kWave;
+        int gmax = (int)std::min<long long>((kDnsLdsBytes - slack) / unit, 1 << 20);
+        if (gmax < 1 && unit + slack <= kDnsLdsMax) gmax = 1;
+        if (gmax < ksr) continue;
+        const int ahead = std::max(1, kDnsRounds * threads / (2 * q->PX));  // groups loaded ahead
+        int Cg = std::min({ahead, gmax, ngroups});
+        if (Cg < ngroups && gmax / 2 >= ksr) Cg = std::min(Cg, gmax / 2);
+        Cg = std::max(ksr, Cg / ksr * ksr);
+        q->ksr = ksr;
+        q->ksp = ksp;
+        q->NBW = nbw;
+        q->Cg = Cg;
+        q->nchunks = (ngroups + Cg - 1) / Cg;
+        q->nbuf = (q->nchunks > 1 && 2 * Cg <= gmax) ? 2 : 1;
+        q->lds_bytes = std::max((size_t)(q->nbuf * Cg * unit + slack), epi);
+        return true;
+    }
+    return false;
 }
 
 // Tile rows: among the heights whose tile fits 8 pixel blocks (even heights
 // when pooling), the least modelled work, tiles x (blocks + 1): a wave's MFMAs
-// per channel pair (one per block and tap) plus about one block's worth for
-// the pair's A fragments, which each block reuses; provided the grid keeps at
-// least 1536 waves (six per SIMD over the run) when any height can, ties going
-// to the grid with more waves. Measured on 14x14 (256 channels), 28x28 pooled
-// and 56x56 layers: the picks are each layer's fastest tiling of the sweep.
-bool plan_dense(int N, int C, int K, int Wp, int Ho, int R, int S, bool pool, DensePlan *pl) {
+// per channel group (one set per block and tap) plus about one block's worth
+// for the group's A fragments, which each block reuses; provided the grid keeps
+// at least 1536 waves (six per SIMD over the run) when any height can, ties
+// going to the grid with more waves. Measured on 14x14 (256 channels), 28x28
+// pooled and 56x56 layers: the picks are each layer's fastest tiling of the sweep.
+bool plan_dense(int N, int C, int K, int H, int W, int pad, int Wp, int Ho, int Wo, int R, int S, bool pool,
+                DensePlan *pl) {
     DensePlan p;
     p.nw = dense_waves(K);
     p.nkt = (K + kDnsTile * p.nw - 1) / (kDnsTile * p.nw);
@@ -468,19 +682,11 @@ bool plan_dense(int N, int C, int K, int Wp, int Ho, int R, int S, bool pool, De
         q.NB = (th * Wp + kDnsTile - 1) / kDnsTile;
         if (q.NB > kDnsMaxBlocks) break;
         q.ntiles_y = (Ho + th - 1) / th;
-        // A channel's staged rows must cover every B read: the last block's
-        // last pixel shifted by the largest tap offset. Slots are 16-byte
-        // aligned for the 16-byte copies.
-        q.PLp = round_up(std::max((th + R - 1) * Wp, q.NB * kDnsTile + (R - 1) * Wp + S - 1), 4);
-        const int cmax = kDnsLdsBytes / (2 * q.PLp * (int)sizeof(float)) / 2 * 2;
-        if (cmax < 2) continue;
-        q.Cc = std::min(cmax, round_up(C, 2));
-        q.nchunks = (C + q.Cc - 1) / q.Cc;
-        // The copy offsets of one chunk are 32-bit byte offsets (and int floats).
-        if (((long long)(q.Cc - 1) * (Ho + R - 1) * Wp + q.PLp + kDnsBlock) * 4 >= (1LL << 31)) continue;
         const long long base_waves = (long long)N * q.ntiles_y * q.nkt * q.nw;
-        q.ks = dense_ks(base_waves, q.nw, q.NB, q.Cc);
-        const long long waves = base_waves * q.ks;
+        if (!dense_layout_tile(C, Wp, Wo, R, S, pool, dense_split(base_waves, q.nw), &q)) continue;
+        // The load offsets of one chunk are 32-bit byte offsets.
+        if ((long long)q.Cg * kDnsGroup * (H + 2LL * pad) * Wp * 4 >= (1LL << 31)) continue;
+        const long long waves = base_waves * q.ksr * q.ksp;
         const long long cost = (long long)q.ntiles_y * (q.NB + 1);
         bool better;
         if (best.TH == 0) {
@@ -502,11 +708,6 @@ bool plan_dense(int N, int C, int K, int Wp, int Ho, int R, int S, bool pool, De
     }
     if (best.TH == 0) return false;
     p = best;
-    size_t lds = (size_t)2 * p.Cc * p.PLp * sizeof(float);
-    if (pool) lds = std::max(lds, (size_t)p.nw * kDnsPoolCh * p.NB * kDnsTile * sizeof(float));
-    if (p.ks > 1) lds = std::max(lds, (size_t)p.nw * p.NB * 16 * kWave * sizeof(float));
-    if (lds > (size_t)kDnsLdsBytes) return false;
-    p.lds_bytes = lds;
     const long long wgs = (long long)N * p.ntiles_y * p.nkt;
     if (wgs > 0x7fffffffLL) return false;
     p.total_wgs = (int)wgs;
@@ -533,8 +734,8 @@ int prepare_dense(int N, int C, int H, int W, int K, int R, int S, int pad, uint
     if (!out_extent(H, R, pad, &Ho) || !out_extent(W, S, pad, &Wo)) return SPCONV_EINVAL;
     if (pool && (Ho < 2 || Wo < 2)) return SPCONV_EINVAL;
     DensePlan pl;
-    if (!plan_dense(N, C, K, (int)Wp, Ho, R, S, pool, &pl)) return SPCONV_EINVAL;
-    if (!pick_dense(R, S, pl.NB, pool)) return SPCONV_EINVAL;
+    if (!plan_dense(N, C, K, H, W, pad, (int)Wp, Ho, Wo, R, S, pool, &pl)) return SPCONV_EINVAL;
+    if (!pick_dense(R, S, pl.NBW, pool)) return SPCONV_EINVAL;
     DenseArgs a;
     a.N = N;
     a.C = C;
@@ -556,24 +757,23 @@ int prepare_dense(int N, int C, int H, int W, int K, int R, int S, int pad, uint
                   !div_magic((uint32_t)a.Wq, &a.wq_magic, &a.wq_shift))))
         return SPCONV_EINVAL;
     a.relu = (flags & SPCONV_RELU) ? 1 : 0;
-    a.unpadded = (flags & SPCONV_UNPADDED_INPUT) ? 1 : 0;
-    a.H = H;
-    a.W = W;
-    a.pad = pad;
-    a.rows_in = pl.TH + R - 1;
+    const bool unpadded = (flags & SPCONV_UNPADDED_INPUT) != 0;
+    a.IH = unpadded ? H : (int)Hp;
+    a.IW = unpadded ? W : (int)Wp;
+    a.ipad = unpadded ? pad : 0;
     a.TH = pl.TH;
     a.ntiles_y = pl.ntiles_y;
     a.nw = pl.nw;
-    a.ks = pl.ks;
+    a.ksr = pl.ksr;
+    a.ksp = pl.ksp;
     a.nkt = pl.nkt;
-    a.Cc = pl.Cc;
+    a.Cg = pl.Cg;
     a.nchunks = pl.nchunks;
-    a.PLp = pl.PLp;
-    if (!unit_step(a.rows_in, pl.nw * pl.ks, &a.row_units) ||
-        !unit_step((pl.PLp + kDnsBlock - 1) / kDnsBlock, pl.nw * pl.ks, &a.blk_units))
-        return SPCONV_EINVAL;
-    a.buf_floats = pl.Cc * pl.PLp;
-    a.total_floats = (size_t)N * C * Hp * Wp;
+    a.nbuf = pl.nbuf;
+    a.PX = pl.PX;
+    a.tasks = 2 * pl.Cg * pl.PX;
+    a.buf_bytes = pl.Cg * pl.PX * kDnsPxBytes;
+    if (!div_magic((uint32_t)pl.PX, &a.px_magic, &a.px_shift)) return SPCONV_EINVAL;
     a.total_wgs = pl.total_wgs;
     const long long op = opt ? opt->out_pad : 0;
     const long long rp = (opt && opt->residual) ? opt->residual_pad : 0;
@@ -602,11 +802,11 @@ extern "C" int spconv_forward_dense(const float *in_padded, int N, int C, int H,
     DenseArgs a;
     const int rc = prepare_dense(N, C, H, W, K, R, S, pad, flags, opt, &pl, &a);
     if (rc != SPCONV_OK) return rc;
-    DenseKernel kern = pick_dense(R, S, pl.NB, (flags & SPCONV_MAXPOOL2X2) != 0);
+    DenseKernel kern = pick_dense(R, S, pl.NBW, (flags & SPCONV_MAXPOOL2X2) != 0);
     const float *residual = opt ? opt->residual : nullptr;
     // Raised once per instance to the family's budget (see raise_lds_limit).
-    if (!raise_lds_limit((const void *)kern, kDnsLdsBytes)) return SPCONV_EHIP;
-    hipLaunchKernelGGL(kern, dim3((unsigned)pl.total_wgs), dim3((unsigned)(pl.nw * pl.ks * kWave)), pl.lds_bytes, stream, a,
+    if (!raise_lds_limit((const void *)kern, kDnsLdsMax)) return SPCONV_EHIP;
+    hipLaunchKernelGGL(kern, dim3((unsigned)pl.total_wgs), dim3((unsigned)(pl.nw * pl.ksr * pl.ksp * kWave)), pl.lds_bytes, stream, a,
                        in_padded, packed, bias, residual, out);
     return hipGetLastError() == hipSuccess ? SPCONV_OK : SPCONV_EHIP;
 }
@@ -624,10 +824,10 @@ extern "C" int spconv_dense_plan(int N, int C, int H, int W, int K, int R, int S
     info->channels_per_wave = kDnsTile;
     info->tile_rows = pl.TH;
     info->tiles_per_image = pl.ntiles_y;
-    info->channels_per_chunk = pl.Cc;
+    info->channels_per_chunk = std::min(pl.Cg * kDnsGroup, C);
     info->chunks = pl.nchunks;
     info->workgroups = pl.total_wgs;
-    info->threads_per_workgroup = pl.nw * pl.ks * kWave;
+    info->threads_per_workgroup = pl.nw * pl.ksr * pl.ksp * kWave;
     info->lds_bytes = (int64_t)pl.lds_bytes;
     info->lds_channel_floats = info->lds_row_pitch = info->lds_col_shift = 0;
     info->launch_workgroups = pl.total_wgs;

@@ -530,12 +530,9 @@ class SparseConvLayer:
             self._lowered_cache[key] = t
         return self._lowered_cache[key]
 
-    # The dense kernel stages an unpadded input one image row per LDS-DMA
-    # instruction, and on MI355X such a copy costs about the same per
-    # instruction up to 1 KiB; rows narrower than this many bytes make the
-    # copies slower than a separate pad pass (measured: 224-byte rows 3.4x the
-    # time of 1 KiB copies for the same bytes, 896-byte rows on par).
-    MIN_ROW_BYTES_PAD_IN_KERNEL = 768
+    # The dense kernel reads its input through registers, so forming the border
+    # costs it nothing (14x14, 256 channels, batch 32: the pad pass it saves took
+    # 6.4 us).
     # The stride-1 sparse kernel fills whole 1 KiB LDS blocks per instruction
     # whatever the row length, 16 bytes per lane when the rows are whole 16-byte
     # groups: then forming the border costs less than a pad pass (measured at
@@ -552,13 +549,11 @@ class SparseConvLayer:
 
     def pads_in_kernel(self, N: int) -> bool:
         """Whether ``forward`` forms the zero border in the kernel (it can, and
-        that beats a pad pass: rows of whole 16-byte groups for the sparse
-        stride-1 kernel, wide enough rows for the dense kernel)."""
+        that beats a pad pass: always for the dense kernel, for the sparse
+        stride-1 kernel on rows of whole 16-byte groups)."""
         if not self.can_pad_in_kernel(N):
             return False
-        if self.path == "dense":
-            return 4 * self.W >= self.MIN_ROW_BYTES_PAD_IN_KERNEL
-        return self.W % 4 == 0
+        return self.path == "dense" or self.W % 4 == 0
 
     def forward(self, x, out=None, stream=None, out_pad: int = 0, residual=None, residual_pad: int = 0, xp=None,
                 pad_in_kernel: bool | None = None):

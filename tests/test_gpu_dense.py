@@ -134,3 +134,66 @@ def test_dense_and_sparse_agree(sp):
     ref, ab = oracle.conv(layer.x, layer.w, layer.mask, layer.bias, 1, 1, True, False)
     for path, o in outs.items():
         check_close(o.cpu().numpy(), ref, ab, path)
+
+
+# N, C, K, H, W, R, pool: channel counts around the 16-channel groups, K around
+# the 32-channel tiles, one to eight pixel blocks shared by one to four waves
+# (single rows and blocks past the last stored pixel among them).
+GROUP_CASES = [
+    (1, 1, 1, 3, 3, 3, False),
+    (1, 15, 31, 5, 34, 3, False),
+    (2, 16, 32, 9, 30, 3, True),
+    (1, 17, 33, 2, 222, 3, False),
+    (1, 33, 65, 8, 62, 3, True),
+    (3, 48, 129, 7, 7, 3, False),
+    (2, 8, 64, 6, 253, 3, False),
+    (1, 40, 40, 12, 125, 3, True),
+    (2, 31, 97, 11, 33, 1, False),
+    (1, 130, 36, 10, 64, 1, True),
+]
+
+
+@pytest.mark.parametrize("case", GROUP_CASES)
+def test_dense_channel_groups_and_unpadded_input(sp, case):
+    """Against the oracle, and the unpadded input against the padded one bit for bit."""
+    import torch
+    N, C, K, H, W, R, pool = case
+    layer = synth.random_layer(8100 + C, N, C, K, H, W, R, R, 1, R // 2, 0.6, True, pool, True, False)
+    L = _dense_layer(sp, layer)
+    say("dense groups", case, L.plan(N))
+    x = torch.from_numpy(layer.x).cuda()
+    out = L.run(x)
+    raw = L.forward(x, pad_in_kernel=True)
+    torch.cuda.synchronize()
+    ref, ab = oracle.conv(layer.x, layer.w, layer.mask, layer.bias, 1, layer.pad, True, pool)
+    check_close(out.cpu().numpy(), ref, ab, f"dense {case}")
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), raw.cpu().numpy().view(np.uint32))
+
+
+def test_dense_extreme_values(sp):
+    """Infinities, NaN and values that round to infinity in bf16 give what fp32
+    arithmetic over every tap gives, and leave the other outputs alone; tiny
+    values keep their leading bits."""
+    import torch
+    layer = synth.random_layer(8200, 2, 20, 40, 12, 13, 3, 3, 1, 1, 1.0, False, False, True, False)
+    layer.w[layer.w == 0] = 0.5
+    layer.w[3] *= 1e-6
+    layer.x[0, 2, 4, 5] = np.inf
+    layer.x[0, 7, 9, 9] = -np.inf
+    layer.x[0, 1, 0, 12] = np.nan
+    layer.x[1, 3, 6, 6] = 3.4028e38
+    layer.x[1, 5, 2, 2] = 1e-30
+    L = sp.SparseConvLayer(layer.w, layer.mask, layer.bias, 12, 13, 1, 1, False, False, path="dense")
+    say("dense extreme values", L.plan(2))
+    out = L.run(torch.from_numpy(layer.x).cuda())
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    with np.errstate(all="ignore"):
+        ref = torch.nn.functional.conv2d(torch.from_numpy(layer.x).double(), torch.from_numpy(layer.w).double(),
+                                         torch.from_numpy(layer.bias).double(), padding=1).numpy()
+        ab = torch.nn.functional.conv2d(torch.from_numpy(np.abs(layer.x)).double(),
+                                        torch.from_numpy(np.abs(layer.w)).double(), padding=1).numpy()
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(np.isinf(got) & (ab < 1e38), np.isinf(ref) & (ab < 1e38))
+    fin = np.isfinite(ref) & (ab < 3e38)
+    assert (np.abs(got[fin] - ref[fin]) <= REL_TOL * ab[fin] + ABS_TOL).all()
