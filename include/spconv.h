@@ -42,9 +42,8 @@ extern "C" {
 #define SPCONV_MAXPOOL2X2 2u /* 2x2 window, stride 2, applied after the ReLU */
 /* The input is the unpadded [N][C][H][W] tensor: the kernel forms the zero
  * border itself while staging the input in LDS, so no padded copy is made
- * (the pad step fused into the convolution). Stride-1 plans and the dense
- * path only: a layer whose plan (spconv_plan) is SPCONV_KERNEL_GENERIC gets
- * SPCONV_EINVAL. The results are bit-identical to the padded input's. */
+ * (the pad step fused into the convolution). Stride-1 layers and the dense
+ * path only: a strided layer gets SPCONV_EINVAL. The results are bit-identical to the padded input's. */
 #define SPCONV_UNPADDED_INPUT 4u
 
 /*
@@ -289,16 +288,18 @@ int spconv_pack_lowered(int N, int C, int H, int W, const spconv_csr *csr, int K
 
 /* Kernel families reported by spconv_plan. */
 #define SPCONV_KERNEL_STRIDE1 1 /* stride 1: channel-chunked LDS staging, lanes own padded-width pixels */
-#define SPCONV_KERNEL_GENERIC 2 /* any stride */
+#define SPCONV_KERNEL_GENERIC 2 /* any stride, fewer than 8 input channels */
 #define SPCONV_KERNEL_DENSE 3   /* dense filter on the matrix cores (spconv_forward_dense) */
 /* spconv_kernel_variants only: the stride-1 tilings also built to run several
  * work items per workgroup with a lowered stream (the launch takes that form
  * when the plan has more work items than launch_workgroups). */
 #define SPCONV_KERNEL_STRIDE1_TILED 4
+#define SPCONV_KERNEL_MATRIX 5  /* CSR filter on the matrix cores: strided layers of 8 or more input channels */
 
 typedef struct spconv_plan_info {
-    int32_t kernel;                /* SPCONV_KERNEL_STRIDE1, _GENERIC or _DENSE */
-    int32_t pixels_per_lane;       /* virtual output pixels per lane per image; dense: 32-pixel blocks per tile */
+    int32_t kernel;                /* SPCONV_KERNEL_STRIDE1, _GENERIC, _DENSE or _MATRIX */
+    int32_t pixels_per_lane;       /* virtual output pixels per lane per image; dense: 32-pixel blocks per tile;
+                                    * matrix: 16-pixel blocks per wave */
     int32_t images_per_group;      /* images sharing one workgroup's tile */
     int32_t channels_per_wave;     /* output channels (CSR rows) per wave; generic kernel: per workgroup */
     int32_t tile_rows;             /* output rows per spatial tile */
@@ -320,7 +321,8 @@ typedef struct spconv_plan_info {
      * on a tiling of SPCONV_KERNEL_STRIDE1_TILED with more than 256 work
      * items, 256 workgroups (one per CU) that take the work items in turn. */
     int32_t launch_workgroups;
-    /* Stride-1 kernel with a lowered stream (opt->lowered non-NULL), unpooled,
+    /* Matrix kernel: output pixels per tile (tile_rows rows of one width).
+     * Stride-1 kernel with a lowered stream (opt->lowered non-NULL), unpooled,
      * one image per tile: virtual pixels per row-spanning tile. Tile t of an
      * image then covers its virtual pixels [t * tile_pixels, (t+1) *
      * tile_pixels) (pixel y*lds_row_pitch + x), starting in any column, and
@@ -351,6 +353,7 @@ int spconv_plan(int N, int C, int H, int W, const spconv_csr *csr, int K, int R,
  *                          several work items per workgroup
  *   SPCONV_KERNEL_GENERIC  (pixels_per_lane, 0, channels_per_workgroup, pool)
  *   SPCONV_KERNEL_DENSE    (R, S, pixel blocks per tile, pool)
+ *   SPCONV_KERNEL_MATRIX   (16-pixel blocks per wave, 0, channels per wave, pool)
  * with pool 0 or 1 and the other fields as spconv_plan_info reports them.
  * variants  host array of 4*capacity int32, nullable when capacity is 0; the
  *           first min(count, capacity) tuples are written.

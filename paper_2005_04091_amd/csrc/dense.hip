@@ -9,8 +9,8 @@
 // value is the sum of three bf16 parts, x = h + m + l (each the bf16 rounding
 // of what the parts before it leave, so the sum is exact), and a product takes
 // the six part products of weight 2^-16 or more, hh + hm + mh + mm + hl + lh,
-// on v_mfma_f32_32x32x16_bf16 with fp32 sums (what is dropped is below 2^-24
-// of the product). Six of them take 192 cycles for 16 channels, where the fp32
+// on v_mfma_f32_32x32x16_bf16 with fp32 sums (what is dropped is at most
+// 2^-23 of the product and 2^-26 on average). Six of them take 192 cycles for 16 channels, where the fp32
 // MFMA (32x32x2) takes 512.
 //  * a workgroup owns (image, tile of TH output rows, 32*nw output channels);
 //    the tile's NB blocks of 32 consecutive virtual pixels are dealt to ksp
@@ -35,6 +35,7 @@
 
 #include "common.h"
 #include "dense_layout.h"
+#include "split.h"
 #include "spconv.h"
 
 __attribute__((visibility("hidden"))) int dense_kernel_variants(int32_t *variants, int32_t capacity, int32_t *count);
@@ -42,10 +43,6 @@ __attribute__((visibility("hidden"))) int dense_kernel_variants(int32_t *variant
 namespace {
 
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kDnsTile = dense_layout::kTile;  // MFMA tile: 32 channels x 32 pixels
 constexpr int kDnsMaxThreads = 512;       // nw * ksr * ksp waves per workgroup, at most 8
@@ -87,34 +84,6 @@ struct DenseArgs {
     // row i - ipad, column x - ipad (the padded tensor itself: ipad = 0)
     int IH, IW, ipad;
 };
-
-// bf16 parts of eight floats, two to a register (see the file comment).
-struct Parts {
-    u32x4_t h, m, l;
-};
-
-// Parts of floats 2*i and 2*i + 1; with r what the parts before leave.
-__device__ __forceinline__ void split2(Parts &p, int i, float x, float y) {
-    const f32x2_t v = {x, y};
-    const uint32_t hb = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-    const f32x2_t r1 = {x - __uint_as_float(hb << 16), y - __uint_as_float(hb & 0xffff0000u)};
-    const uint32_t mb = __builtin_bit_cast(uint32_t, __builtin_convertvector(r1, bf16x2_t));
-    const f32x2_t r2 = {r1.x - __uint_as_float(mb << 16), r1.y - __uint_as_float(mb & 0xffff0000u)};
-    p.h[i] = hb;
-    p.m[i] = mb;
-    p.l[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r2, bf16x2_t));
-}
-
-// Buffer descriptor of a wave-uniform range. Parts of its address come from
-// divisions and 64-bit products, which run on the vector unit: without the way
-// back to scalars every load through it becomes a loop over the lanes'
-// descriptors.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const float *p, uint32_t bytes) {
-    const uint64_t u = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
-    return __builtin_amdgcn_make_buffer_rsrc((void *)(((uint64_t)hi << 32) | lo), (short)0,
-                                             (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000);
-}
 
 // One staging task: eight channels of one staged pixel of a chunk.
 struct StageTask {

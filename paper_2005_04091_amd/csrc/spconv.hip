@@ -39,6 +39,7 @@
 #include <vector>
 
 #include "common.h"
+#include "matrix.h"
 #include "spconv.h"
 
 // Instances of the dense kernel (dense.hip), for spconv_kernel_variants.
@@ -2316,6 +2317,19 @@ long long lowered_words(const Plan &pl, long long nnz) {
     return 4LL * lowered_headers(pl) + 2LL * (nnz + kLwPad);
 }
 
+// Whether a call without a lowered stream runs on the matrix cores (matrix.hip):
+// strided layers of at least one whole octet of input channels. Measured from
+// one 16x16 image of 16 channels to 56x56, batch 32, 64 to 128 channels, filters
+// of 1x1 to 5x5 and densities 0.05 to 0.5: 7.7 to 53 us there against 10 to 473 us
+// of the any-stride kernel. With 3 channels, where most of an octet is
+// padding, that kernel is the faster one at low density (8.7 against 11.6 us on
+// 100x100, batch 8).
+bool use_matrix(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, uint32_t flags, long long nnz,
+                MatrixPlan *mp) {
+    if (stride == 1 || C < 8) return false;
+    return matrix_plan(N, C, H, W, K, R, S, stride, pad, (flags & SPCONV_MAXPOOL2X2) != 0, nnz, mp);
+}
+
 int apply_epilogue(const spconv_options *opt, FwdArgs *a) {
     if (!opt) return SPCONV_OK;
     if (opt->out_pad < 0 || (opt->residual && opt->residual_pad < 0)) return SPCONV_EINVAL;
@@ -2346,6 +2360,13 @@ extern "C" int spconv_forward_ex(const float *in_padded, int N, int C, int H, in
     rc = apply_epilogue(opt, &a);
     if (rc != SPCONV_OK) return rc;
     const float *residual = opt ? opt->residual : nullptr;
+    MatrixPlan mp;
+    if (!(opt && opt->lowered) && use_matrix(N, C, H, W, K, R, S, stride, pad, flags, csr->nnz, &mp)) {
+        const MatrixCall c = {N, C, H, W, K, R, S, stride, pad, a.Ho, a.Wo, (flags & SPCONV_MAXPOOL2X2) != 0,
+                              (flags & SPCONV_UNPADDED_INPUT) != 0, a.relu, a.out_pad, a.opitch, a.res_pad, a.rpitch,
+                              a.oplane, a.rplane};
+        return matrix_launch(mp, c, in_padded, csr->rowptr, csr->offset, csr->vals, bias, residual, out, stream);
+    }
     // 16-byte row copies need a 16-byte aligned tensor; otherwise the same
     // layout is filled 4 bytes per lane.
     if (a.dma16 && (reinterpret_cast<uintptr_t>(in_padded) & 15) != 0) a.dma16 = 0;
@@ -2397,6 +2418,23 @@ extern "C" int spconv_plan(int N, int C, int H, int W, const spconv_csr *csr, in
     rc = apply_epilogue(opt, &a);
     if (rc != SPCONV_OK) return rc;
     const bool s1 = pl.kind == Kind::kStride1;
+    MatrixPlan mp;
+    if (!(opt && opt->lowered) && use_matrix(N, C, H, W, K, R, S, stride, pad, flags, csr->nnz, &mp)) {
+        info->kernel = SPCONV_KERNEL_MATRIX;
+        info->pixels_per_lane = mp.NBX;
+        info->images_per_group = 1;
+        info->channels_per_wave = 16 * mp.RB;
+        info->tile_rows = mp.TH;
+        info->tiles_per_image = mp.nty * mp.ntx;
+        info->channels_per_chunk = std::min(8 * mp.O, C);
+        info->chunks = mp.nchunks;
+        info->workgroups = info->launch_workgroups = mp.total_wgs;
+        info->threads_per_workgroup = 512;
+        info->lds_bytes = (int64_t)mp.lds_bytes;
+        info->lds_channel_floats = info->lds_row_pitch = info->lds_col_shift = 0;
+        info->tile_pixels = mp.TH * mp.TW;
+        return SPCONV_OK;
+    }
     info->kernel = s1 ? SPCONV_KERNEL_STRIDE1 : SPCONV_KERNEL_GENERIC;
     info->pixels_per_lane = s1 ? pl.PI : pl.P;
     info->images_per_group = pl.ipw;
@@ -2420,6 +2458,10 @@ extern "C" int spconv_plan(int N, int C, int H, int W, const spconv_csr *csr, in
 extern "C" int spconv_kernel_variants(int32_t kernel, int32_t *variants, int32_t capacity, int32_t *count) {
     if (!count || capacity < 0 || (capacity > 0 && !variants)) return SPCONV_EINVAL;
     if (kernel == SPCONV_KERNEL_DENSE) return dense_kernel_variants(variants, capacity, count);
+    if (kernel == SPCONV_KERNEL_MATRIX) {
+        matrix_variants(variants, capacity, count);
+        return SPCONV_OK;
+    }
     if (kernel != SPCONV_KERNEL_STRIDE1 && kernel != SPCONV_KERNEL_GENERIC && kernel != SPCONV_KERNEL_STRIDE1_TILED)
         return SPCONV_EINVAL;
     int n = 0;

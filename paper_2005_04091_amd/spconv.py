@@ -33,6 +33,7 @@ SPCONV_KERNEL_STRIDE1 = 1
 SPCONV_KERNEL_GENERIC = 2
 SPCONV_KERNEL_DENSE = 3
 SPCONV_KERNEL_STRIDE1_TILED = 4
+SPCONV_KERNEL_MATRIX = 5
 SPCONV_PATH_SPARSE = 1
 SPCONV_PATH_DENSE = 2
 

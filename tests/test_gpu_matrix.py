@@ -1,0 +1,152 @@
+"""GPU parity of the matrix-core kernel for CSR filters (strided layers of eight
+or more input channels) against the oracle, whole tensors at the layer tolerance
+1e-5 * sum|w*x| + 1e-6. Its products are fp32 values as three bf16 parts with
+fp32 sums, so the tolerance is that of the other kernels. Cases cover every
+compiled instance, channel counts around the octets and chunks, output channels
+around the 16-channel row blocks, strides 2 and 3, filters of 1x1 to 7x7 and
+unequal sides, rows of several tiles, empty and full filters, and rows with more
+entries per chunk than the prefetched queue holds. Every case prints its name
+and plan before touching the GPU.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2005_04091_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+REL_TOL = 1e-5
+ABS_TOL = 1e-6
+
+
+@pytest.fixture(scope="module")
+def sp():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2005_04091_amd import spconv
+    return spconv
+
+
+def check_close(got, ref, ab, what):
+    got = np.asarray(got, np.float64)
+    assert got.shape == ref.shape, (got.shape, ref.shape)
+    bad = ~(np.abs(got - ref) <= REL_TOL * ab + ABS_TOL)
+    assert not bad.any(), f"{what}: {int(bad.sum())} of {bad.size} outputs out of tolerance"
+
+
+# N, C, K, H, W, R, S, stride, pad, density, pool, skew
+CASES = [
+    (3, 8, 55, 6, 5, 1, 1, 3, 0, 0.1, False, False),      # (2 pixel blocks, 16 channels)
+    (5, 25, 9, 6, 7, 7, 7, 3, 3, 0.05, True, False),
+    (8, 8, 29, 96, 77, 1, 1, 2, 0, 0.2, False, False),    # (4, 16)
+    (2, 10, 146, 50, 67, 1, 1, 2, 0, 0.2, True, False),
+    (22, 11, 87, 78, 94, 1, 1, 2, 0, 0.13, False, False),  # (4, 32)
+    (34, 14, 84, 65, 66, 1, 1, 2, 0, 0.16, True, False),
+    (30, 13, 239, 27, 18, 1, 1, 2, 0, 0.06, False, False),  # (7, 16)
+    (5, 9, 8, 186, 193, 3, 3, 2, 1, 0.1, True, False),
+    (1, 8, 1, 3, 3, 3, 3, 2, 1, 1.0, False, False),       # smallest
+    (2, 9, 16, 7, 9, 3, 3, 2, 1, 0.5, False, False),
+    (2, 15, 17, 8, 8, 3, 3, 2, 0, 0.3, True, False),
+    (1, 16, 31, 9, 31, 3, 1, 2, 1, 0.4, False, False),
+    (1, 17, 33, 31, 9, 1, 3, 2, 1, 0.4, False, False),
+    (2, 33, 65, 20, 21, 5, 5, 2, 2, 0.2, False, True),
+    (1, 24, 40, 12, 300, 3, 3, 2, 1, 0.2, False, False),  # rows of several tiles
+    (1, 24, 24, 31, 33, 3, 3, 3, 1, 0.0, False, False),   # no entries: act(bias)
+    (2, 130, 20, 13, 14, 3, 3, 2, 1, 1.0, True, False),   # more entries per chunk than the queue
+    (4, 64, 128, 56, 56, 3, 3, 2, 1, 0.2, False, False),
+    (2, 40, 70, 33, 47, 3, 3, 4, 2, 0.3, False, True),
+]
+
+
+def _layer(i):
+    N, C, K, H, W, R, S, st, pad, d, pool, skew = CASES[i]
+    return synth.random_layer(9500 + i, N, C, K, H, W, R, S, st, pad, d, True, pool, i % 3 != 2, skew)
+
+
+def _on_device(sp, layer):
+    N, C, H, W, K, R, S = layer.shape
+    L = sp.SparseConvLayer(layer.w, layer.mask, layer.bias, H, W, layer.stride, layer.pad, True, layer.pool)
+    plan = L.plan(N)
+    print("[case]", layer.shape, layer.stride, plan, flush=True)
+    assert plan["kernel"] == sp.SPCONV_KERNEL_MATRIX
+    return L, plan
+
+
+@pytest.mark.parametrize("i", range(len(CASES)))
+def test_strided_layers_and_epilogue_options(sp, i):
+    import torch
+    layer = _layer(i)
+    N, C, H, W, K, R, S = layer.shape
+    L, _ = _on_device(sp, layer)
+    xp = L.pad_input(torch.from_numpy(layer.x).cuda())
+    out = L.forward_padded(xp)
+    res = np.random.default_rng(i).uniform(-1, 1, (N, K, (H + 2 * layer.pad - R) // layer.stride + 1,
+                                                   (W + 2 * layer.pad - S) // layer.stride + 1)).astype(np.float32)
+    res_dev = torch.from_numpy(np.pad(res, ((0, 0), (0, 0), (1, 1), (1, 1)))).cuda()
+    buf = torch.full((N, K, L.Ho + 4, L.Wo + 4), float("nan"), device="cuda")
+    L.forward_padded(xp, out=buf, out_pad=2, residual=res_dev, residual_pad=1)
+    torch.cuda.synchronize()
+    ref, ab = oracle.conv(layer.x, layer.w, layer.mask, layer.bias, layer.stride, layer.pad, True, layer.pool)
+    check_close(out.cpu().numpy(), ref, ab, f"{CASES[i]}")
+    ref, ab = oracle.conv(layer.x, layer.w, layer.mask, layer.bias, layer.stride, layer.pad, True, layer.pool,
+                          residual=res)
+    got = buf.cpu().numpy()
+    check_close(got[:, :, 2:-2, 2:-2], ref, ab, f"{CASES[i]} residual")
+    got[:, :, 2:-2, 2:-2] = 0
+    assert not got.view(np.uint32).any(), "the border holds something else than +0.0"
+
+
+def test_every_instance_has_a_case(sp):
+    have = {(p["pixels_per_lane"], 0, p["channels_per_wave"], int(_layer(i).pool))
+            for i in range(len(CASES)) for p in [_on_device(sp, _layer(i))[1]]}
+    assert have == set(sp.spconv_kernel_variants(sp.SPCONV_KERNEL_MATRIX))
+
+
+def test_extreme_values_touch_only_the_outputs_that_read_them(sp):
+    """Infinities, NaN and values that round to infinity in bf16: each output is
+    what its own entries give in fp32 (a zero of the filter reads nothing)."""
+    import torch
+    layer = synth.random_layer(9600, 2, 20, 40, 21, 23, 3, 3, 2, 1, 0.3, False, False, True, False)
+    layer.x[0, 2, 4, 5] = np.inf
+    layer.x[0, 7, 9, 9] = -np.inf
+    layer.x[0, 1, 0, 12] = np.nan
+    layer.x[1, 3, 6, 6] = 3.4028e38
+    L, _ = _on_device(sp, layer)
+    L.flags = 0  # no ReLU, which hides NaN and negative infinities
+    out = L.forward_padded(L.pad_input(torch.from_numpy(layer.x).cuda()))
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    K = layer.w.shape[0]
+    xp = np.pad(layer.x.astype(np.float64), ((0, 0), (0, 0), (1, 1), (1, 1)))
+    ref = np.repeat(np.repeat(layer.bias.astype(np.float64)[None, :, None, None], L.Ho, 2), L.Wo, 3).repeat(2, 0)
+    ab = np.zeros_like(ref)
+    with np.errstate(all="ignore"):
+        for k in range(K):
+            for c, r, s in np.argwhere(layer.mask[k]):
+                v = xp[:, c, r:r + 2 * L.Ho - 1:2, s:s + 2 * L.Wo - 1:2]
+                ref[:, k] += layer.w[k, c, r, s] * v
+                ab[:, k] += np.abs(layer.w[k, c, r, s] * v)
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    fin = np.isfinite(ref) & (ab < 3e38)
+    assert np.array_equal(np.isfinite(got[ab < 3e38]), np.isfinite(ref[ab < 3e38]))
+    assert (np.abs(got[fin] - ref[fin]) <= REL_TOL * ab[fin] + ABS_TOL).all()
+    assert fin.sum() > 0.7 * fin.size
+
+
+def test_replayed_graph_matches_the_eager_call(sp):
+    import torch
+    layer = _layer(17)
+    L, _ = _on_device(sp, layer)
+    xp = L.pad_input(torch.from_numpy(layer.x).cuda())
+    eager = L.forward_padded(xp).clone()
+    out = torch.empty_like(eager)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        L.forward_padded(xp, out=out, stream=torch.cuda.current_stream())
+    for _ in range(3):
+        out.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int32), eager.view(torch.int32))
