@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 from dataclasses import dataclass
+from functools import lru_cache
 from pathlib import Path
 
 import numpy as np
@@ -132,6 +133,7 @@ def spconv_strerror(code: int) -> str:
     return _lib.spconv_strerror(int(code)).decode()
 
 
+@lru_cache(maxsize=1024)  # a function of its integers alone, asked several times per forward call
 def spconv_output_shape(H, W, R, S, stride, pad, flags):
     ho, wo = _c_int(), _c_int()
     _check(_lib.spconv_output_shape(H, W, R, S, stride, pad, flags, ctypes.byref(ho), ctypes.byref(wo)),
@@ -265,19 +267,31 @@ class DeviceCSR:
                                  self.vals.data_ptr())
 
 
+_torch = None
+
+
+def _get_torch():
+    """torch, imported at the first device call (host-side use needs none)."""
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
 def _dev_ptr(t, name):
-    import torch
     if t is None:
         return None
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    torch = _torch or _get_torch()
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a device tensor")
-    if t.dtype != torch.float32 or not t.is_contiguous():
+    if t.dtype is not torch.float32 or not t.is_contiguous():
         raise TypeError(f"{name} must be a contiguous float32 tensor")
     return t.data_ptr()
 
 
 def _check_shape(t, shape, name):
-    if tuple(int(v) for v in t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
 
 
@@ -293,33 +307,36 @@ def _in_elems(N, C, H, W, pad, flags):
     return N * C * (H + 2 * p) * (W + 2 * p)
 
 
-def _stream_of(stream, device):
-    import torch
-    return stream if stream is not None else torch.cuda.current_stream(device)
-
-
-def _empty(shape, device, stream):
-    """A new float32 device tensor whose memory belongs to ``stream``: torch's
-    caching allocator ties a block to the stream current at allocation, and
-    reuses it on that stream once the tensor is freed, so allocating on the
-    stream the kernels run on keeps a freed temporary from being handed out
-    while those kernels still use it."""
-    import torch
-    with torch.cuda.stream(stream):
-        return torch.empty(shape, dtype=torch.float32, device=device)
+def _stream_and_out(stream, device, out, shape):
+    """The raw stream of a call and its output: ``out``, or a new float32 device
+    tensor whose memory belongs to that stream. torch's caching allocator ties a
+    block to the stream current at allocation, and reuses it on that stream once
+    the tensor is freed, so allocating on the stream the kernels run on keeps a
+    freed temporary from being handed out while those kernels still use it. (A
+    call on the current stream, the usual one, needs no switch of streams, which
+    costs more host time than the launch.)"""
+    torch = _torch or _get_torch()
+    if stream is None:
+        raw = torch.cuda.current_stream(device).cuda_stream
+        if out is None:
+            out = torch.empty(shape, dtype=torch.float32, device=device)
+    else:
+        raw = stream.cuda_stream
+        if out is None:
+            with torch.cuda.stream(stream):
+                out = torch.empty(shape, dtype=torch.float32, device=device)
+    return raw, out
 
 
 def spconv_pad_input(x, pad: int, out=None, stream=None):
     """Zero-padded copy of NCHW ``x`` (device), queued on ``stream``."""
     if x.dim() != 4:
         raise ValueError("x must be NCHW")
-    N, C, H, W = (int(v) for v in x.shape)
-    s = _stream_of(stream, x.device)
-    if out is None:
-        out = _empty((N, C, H + 2 * pad, W + 2 * pad), x.device, s)
-    _check_shape(out, (N, C, H + 2 * pad, W + 2 * pad), "out")
-    _check(_lib.spconv_pad_input(_dev_ptr(x, "x"), N, C, H, W, pad, _dev_ptr(out, "out"), s.cuda_stream),
-           "spconv_pad_input")
+    N, C, H, W = x.shape
+    shape = (N, C, H + 2 * pad, W + 2 * pad)
+    s, out = _stream_and_out(stream, x.device, out, shape)
+    _check_shape(out, shape, "out")
+    _check(_lib.spconv_pad_input(_dev_ptr(x, "x"), N, C, H, W, pad, _dev_ptr(out, "out"), s), "spconv_pad_input")
     return out
 
 
@@ -329,14 +346,12 @@ def spconv_resize_pad_input(x, H: int, W: int, pad: int, out=None, stream=None):
     queued on ``stream``."""
     if x.dim() != 4:
         raise ValueError("x must be NCHW")
-    N, C, Hin, Win = (int(v) for v in x.shape)
+    N, C, Hin, Win = x.shape
     shape = (N, C, H + 2 * pad, W + 2 * pad)
-    s = _stream_of(stream, x.device)
-    if out is None:
-        out = _empty(shape, x.device, s)
+    s, out = _stream_and_out(stream, x.device, out, shape)
     _check_shape(out, shape, "out")
-    _check(_lib.spconv_resize_pad_input(_dev_ptr(x, "x"), N, C, Hin, Win, H, W, pad, _dev_ptr(out, "out"),
-                                        s.cuda_stream), "spconv_resize_pad_input")
+    _check(_lib.spconv_resize_pad_input(_dev_ptr(x, "x"), N, C, Hin, Win, H, W, pad, _dev_ptr(out, "out"), s),
+           "spconv_resize_pad_input")
     return out
 
 
@@ -346,14 +361,12 @@ def spconv_forward(xp, N: int, C: int, H: int, W: int, csr: DeviceCSR, K: int, R
     ``xp``: the plain ``spconv_forward`` call (no options, so the planner does
     not see ``csr``'s row skew)."""
     Ho, Wo = spconv_output_shape(H, W, R, S, stride, pad, flags)
-    s = _stream_of(stream, xp.device)
-    if out is None:
-        out = _empty((N, K, Ho, Wo), xp.device, s)
+    s, out = _stream_and_out(stream, xp.device, out, (N, K, Ho, Wo))
     _check_numel(xp, _in_elems(N, C, H, W, pad, flags), "xp")
     _check_numel(out, N * K * Ho * Wo, "out")
     _check_numel(bias, K, "bias")
     _check(_lib.spconv_forward(_dev_ptr(xp, "xp"), N, C, H, W, ctypes.byref(csr.struct), K, R, S, stride, pad,
-                               _dev_ptr(bias, "bias"), flags, _dev_ptr(out, "out"), s.cuda_stream),
+                               _dev_ptr(bias, "bias"), flags, _dev_ptr(out, "out"), s),
            "spconv_forward")
     return out
 
@@ -369,9 +382,7 @@ def spconv_forward_ex(xp, N: int, C: int, H: int, W: int, csr: DeviceCSR, K: int
     tensor from ``spconv_pack_lowered`` for this call) feeds the stride-1
     kernel its entries ready-made."""
     Hs, Ws = spconv_output_shape(H, W, R, S, stride, pad, flags)
-    s = _stream_of(stream, xp.device)
-    if out is None:
-        out = _empty((N, K, Hs + 2 * out_pad, Ws + 2 * out_pad), xp.device, s)
+    s, out = _stream_and_out(stream, xp.device, out, (N, K, Hs + 2 * out_pad, Ws + 2 * out_pad))
     Hc, Wc = spconv_output_shape(H, W, R, S, stride, pad, flags & ~SPCONV_MAXPOOL2X2)
     _check_numel(xp, _in_elems(N, C, H, W, pad, flags), "xp")
     _check_numel(out, N * K * (Hs + 2 * out_pad) * (Ws + 2 * out_pad), "out")
@@ -380,8 +391,8 @@ def spconv_forward_ex(xp, N: int, C: int, H: int, W: int, csr: DeviceCSR, K: int
     hint = csr.max_row_nnz if max_row_nnz is None else max_row_nnz
     lw = None
     if lowered is not None:
-        import torch
-        if not isinstance(lowered, torch.Tensor) or lowered.device.type != "cuda" or lowered.dtype != torch.int32 \
+        torch = _torch or _get_torch()
+        if not isinstance(lowered, torch.Tensor) or not lowered.is_cuda or lowered.dtype is not torch.int32 \
                 or not lowered.is_contiguous():
             raise TypeError("lowered must be a contiguous int32 device tensor")
         lw = lowered.data_ptr()
@@ -389,7 +400,7 @@ def spconv_forward_ex(xp, N: int, C: int, H: int, W: int, csr: DeviceCSR, K: int
                          0 if lowered is None else lowered.numel())
     _check(_lib.spconv_forward_ex(_dev_ptr(xp, "xp"), N, C, H, W, ctypes.byref(csr.struct), K, R, S, stride, pad,
                                   _dev_ptr(bias, "bias"), flags, ctypes.byref(opt), _dev_ptr(out, "out"),
-                                  s.cuda_stream), "spconv_forward_ex")
+                                  s), "spconv_forward_ex")
     return out
 
 
@@ -399,9 +410,7 @@ def spconv_forward_dense(xp, N: int, C: int, H: int, W: int, packed, K: int, R: 
     """The fused conv of ``spconv_forward_ex`` from the packed dense filter
     ``packed`` (device), stride 1."""
     Hs, Ws = spconv_output_shape(H, W, R, S, 1, pad, flags)
-    s = _stream_of(stream, xp.device)
-    if out is None:
-        out = _empty((N, K, Hs + 2 * out_pad, Ws + 2 * out_pad), xp.device, s)
+    s, out = _stream_and_out(stream, xp.device, out, (N, K, Hs + 2 * out_pad, Ws + 2 * out_pad))
     Hc, Wc = spconv_output_shape(H, W, R, S, 1, pad, flags & ~SPCONV_MAXPOOL2X2)
     _check_numel(xp, _in_elems(N, C, H, W, pad, flags), "xp")
     _check_numel(packed, spconv_dense_size(K, C, R, S), "packed")
@@ -411,7 +420,7 @@ def spconv_forward_dense(xp, N: int, C: int, H: int, W: int, packed, K: int, R: 
     opt = spconv_options(out_pad, residual_pad, _dev_ptr(residual, "residual"), 0, None, 0)
     _check(_lib.spconv_forward_dense(_dev_ptr(xp, "xp"), N, C, H, W, _dev_ptr(packed, "packed"), K, R, S, pad,
                                      _dev_ptr(bias, "bias"), flags, ctypes.byref(opt), _dev_ptr(out, "out"),
-                                     s.cuda_stream), "spconv_forward_dense")
+                                     s), "spconv_forward_dense")
     return out
 
 
