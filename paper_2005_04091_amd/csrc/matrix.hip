@@ -584,7 +584,7 @@ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 // nominal 2.5 PFLOP/s on them) and its LDS reads, plus the staging between them
 // (80 instructions per 64 input tasks, 45 per 64 filter entries, the clearing),
 // 1500 cycles per chunk and 12000 per workgroup (its first loads and its
-// epilogue); one workgroup per CU where it takes more than half the LDS. Over
+// epilogue); one workgroup per CU (its registers allow no second). Over
 // 20 tilings of five layers (14x14, 28x28 pooled, 56x56, 56x56 of stride 2,
 // 224x224) a million modelled cycles take 520 to 560 us, and the pick is each
 // layer's fastest.
@@ -653,9 +653,7 @@ bool search_plan(int N, int C, int H, int W, int K, int R, int S, int stride, in
                                                         (double)M * nunits * 12 / 64 * 12);
                         const double bar = nchunks * 1500.0;
                         const double wg = std::max(mfma, ldsr) + (bufs == 2 ? 0.6 : 1.0) * stage + bar + 12000.0;
-                        const double per_cu = lds * 2 <= (size_t)kMatLdsBytes ? 2 : 1;
-                        const double rounds = std::max(1.0, per_cu == 1 ? (double)((wgs + 255) / 256) : (double)wgs / 256.0);
-                        const double time = rounds * wg * (per_cu == 2 ? 0.9 : 1.0);
+                        const double time = (double)((wgs + 255) / 256) * wg;
                         if (best_time < 0 || time < best_time) {
                             best_time = time;
                             best = MatrixPlan{};
