@@ -199,7 +199,9 @@ int spconv_forward(const float *in_padded, int N, int C, int H, int W, const spc
  *           writes for this very call (same N, C, H, W, K, R, S, stride, pad,
  *           flags and max_row_nnz), 16-byte aligned. With it the stride-1
  *           kernel reads its entries ready-made, with scalar loads, instead of
- *           decoding the CSR rows itself (same results bit for bit);
+ *           decoding the CSR rows itself (the bits of its own walk of them; a
+ *           call without a stream may take SPCONV_KERNEL_MATRIX instead, which
+ *           sums in another order);
  *           csr->offset and csr->vals are then not read. Calls whose plan is
  *           not the stride-1 kernel get SPCONV_EINVAL.
  * lowered_words  number of int32 words of `lowered`; must equal
@@ -294,7 +296,10 @@ int spconv_pack_lowered(int N, int C, int H, int W, const spconv_csr *csr, int K
  * work items per workgroup with a lowered stream (the launch takes that form
  * when the plan has more work items than launch_workgroups). */
 #define SPCONV_KERNEL_STRIDE1_TILED 4
-#define SPCONV_KERNEL_MATRIX 5  /* CSR filter on the matrix cores: strided layers of 8 or more input channels */
+/* CSR filter on the matrix cores, for calls without a lowered stream: strided
+ * layers of 8 or more input channels, and stride-1 ones where it is modelled
+ * faster than the stride-1 kernel (dense enough filters). */
+#define SPCONV_KERNEL_MATRIX 5
 
 typedef struct spconv_plan_info {
     int32_t kernel;                /* SPCONV_KERNEL_STRIDE1, _GENERIC, _DENSE or _MATRIX */

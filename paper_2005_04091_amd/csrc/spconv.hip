@@ -1723,6 +1723,7 @@ struct Plan {
     int buf_floats = 0, wv = 0, rows_per_wg = 0, nktiles = 0, total_wgs = 0;
     int span = 0;  // stride-1 kernel: virtual pixels per row-spanning tile (0: tiles of TH whole rows)
     size_t lds_bytes = 0;
+    double time = 0.0;  // stride-1 kernel: modelled cycles
 };
 
 using FwdKernel = void (*)(FwdArgs, const float *, const int32_t *, const int32_t *, const float *, const int32_t *,
@@ -1935,6 +1936,7 @@ bool plan_stride1(int N, int C, int K, int Hp, int Wp, int vp, int shift, int Ho
             best.total_wgs = (int)wgs;
             best.span = span;
             best.lds_bytes = floats * sizeof(float);
+            best.time = time;
         }
     };
     for (int RPW : {1, 2, 4}) {
@@ -2170,10 +2172,44 @@ extern "C" int spconv_resize_pad_input(const float *in, int N, int C, int Hin, i
 
 namespace {
 
+// Whether a call without a lowered stream runs on the matrix cores (matrix.hip).
+//
+// Strided layers of at least one whole octet of input channels: measured from
+// one 16x16 image of 16 channels to 56x56, batch 32, 64 to 128 channels, filters
+// of 1x1 to 5x5 and densities 0.05 to 0.5, 7.7 to 53 us there against 10 to 473 us
+// of the any-stride kernel. With 3 channels, where most of an octet is
+// padding, that kernel is the faster one at low density (8.7 against 11.6 us on
+// 100x100, batch 8).
+//
+// Stride 1: where the two planners' models say so by a margin. In microseconds
+// the stride-1 kernel takes 7.5 + 0.27 per thousand modelled cycles and the
+// matrix kernel 5 + 0.5 (within about 10 % on 44 layers of 7x7 to 224x224, 32 to
+// 512 channels, batch 1 to 32, 1x1 to 5x5, densities 0.05 to 0.6; smaller planes,
+// not among them, keep the stride-1 kernel). The line so
+// falls near density 0.25 at 14x14 and 28x28 and 0.4 at 56x56 and 224x224 in
+// batches of 32, and near 0.15 where one image leaves most CUs without a stride-1
+// workgroup. Measured, stride-1 kernel (with its stream) and matrix kernel: 28x28,
+// 128 channels, pooled 45 / 54 us at density 0.2, 68 / 57 at 0.35; 56x56, 64
+// channels 67 / 66 at 0.35, 93 / 72 at 0.5; 14x14, 256 channels, one image 15 / 17
+// at 0.05, 31 / 21 at 0.2. `pl` is the stride-1 plan for the padded input without
+// the row hint (whose imbalance factor orders tilings and overstates times), so
+// that the choice, and with it the order of the sums, depends on neither.
+bool use_matrix(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, bool pool, long long nnz,
+                const Plan &pl, MatrixPlan *mp) {
+    if (C < 8) return false;
+    if (stride != 1) return matrix_plan(N, C, H, W, K, R, S, stride, pad, pool, nnz, mp);
+    const double walk_us = 7.5 + 0.27e-3 * pl.time;
+    if ((long long)H * W < 49 || walk_us < 15.0 || !matrix_plan(N, C, H, W, K, R, S, stride, pad, pool, nnz, mp)) return false;
+    return walk_us > 1.15 * (5.0 + 0.5e-3 * mp->time);
+}
+
 // Host-side checks of a forward call (everything but the buffer pointers) and
-// its launch plan. Returns SPCONV_OK or SPCONV_EINVAL.
+// its launch plan. Returns SPCONV_OK or SPCONV_EINVAL. With `mp` the call may run
+// on the matrix cores: *mp is then that plan (total_wgs > 0).
 int prepare_forward(int N, int C, int H, int W, const spconv_csr *csr, int K, int R, int S, int stride, int pad,
-                    uint32_t flags, long long max_row_nnz, bool lowered, Plan *plp, FwdArgs *ap) {
+                    uint32_t flags, long long max_row_nnz, bool lowered, Plan *plp, FwdArgs *ap,
+                    MatrixPlan *mp = nullptr) {
+    if (mp) mp->total_wgs = 0;  // not on the matrix cores
     if (!csr) return SPCONV_EINVAL;
     if (N < 1 || C < 1 || H < 1 || W < 1 || K < 1 || R < 1 || S < 1 || stride < 1 || pad < 0) return SPCONV_EINVAL;
     if (flags & ~(SPCONV_RELU | SPCONV_MAXPOOL2X2 | SPCONV_UNPADDED_INPUT)) return SPCONV_EINVAL;
@@ -2212,6 +2248,12 @@ int prepare_forward(int N, int C, int H, int W, const spconv_csr *csr, int K, in
     }
     if (!ok) return SPCONV_EINVAL;
     if (unpadded && pl.kind != Kind::kStride1) return SPCONV_EINVAL;
+    if (mp && !lowered) {
+        Plan plain = pl;  // for the padded input, without the hint
+        if (stride == 1 && (row16 || max_row_nnz > 0))
+            ok = plan_stride1(N, C, K, (int)Hp, (int)Wp, (int)Wp, 0, Ho, Wo, R, S, pool, csr->nnz, 0, false, &plain);
+        if (!ok || !use_matrix(N, C, H, W, K, R, S, stride, pad, pool, csr->nnz, plain, mp)) mp->total_wgs = 0;
+    }
     FwdArgs a;
     a.unpadded = unpadded ? 1 : 0;
     a.vp = pl.kind == Kind::kStride1 ? pl.wv : (int)Wp;
@@ -2317,19 +2359,6 @@ long long lowered_words(const Plan &pl, long long nnz) {
     return 4LL * lowered_headers(pl) + 2LL * (nnz + kLwPad);
 }
 
-// Whether a call without a lowered stream runs on the matrix cores (matrix.hip):
-// strided layers of at least one whole octet of input channels. Measured from
-// one 16x16 image of 16 channels to 56x56, batch 32, 64 to 128 channels, filters
-// of 1x1 to 5x5 and densities 0.05 to 0.5: 7.7 to 53 us there against 10 to 473 us
-// of the any-stride kernel. With 3 channels, where most of an octet is
-// padding, that kernel is the faster one at low density (8.7 against 11.6 us on
-// 100x100, batch 8).
-bool use_matrix(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, uint32_t flags, long long nnz,
-                MatrixPlan *mp) {
-    if (stride == 1 || C < 8) return false;
-    return matrix_plan(N, C, H, W, K, R, S, stride, pad, (flags & SPCONV_MAXPOOL2X2) != 0, nnz, mp);
-}
-
 int apply_epilogue(const spconv_options *opt, FwdArgs *a) {
     if (!opt) return SPCONV_OK;
     if (opt->out_pad < 0 || (opt->residual && opt->residual_pad < 0)) return SPCONV_EINVAL;
@@ -2354,14 +2383,14 @@ extern "C" int spconv_forward_ex(const float *in_padded, int N, int C, int H, in
     if (!in_padded || !out) return SPCONV_EINVAL;
     Plan pl;
     FwdArgs a;
+    MatrixPlan mp;
     int rc = prepare_forward(N, C, H, W, csr, K, R, S, stride, pad, flags, opt ? opt->max_row_nnz : 0,
-                             opt && opt->lowered, &pl, &a);
+                             opt && opt->lowered, &pl, &a, &mp);
     if (rc != SPCONV_OK) return rc;
     rc = apply_epilogue(opt, &a);
     if (rc != SPCONV_OK) return rc;
     const float *residual = opt ? opt->residual : nullptr;
-    MatrixPlan mp;
-    if (!(opt && opt->lowered) && use_matrix(N, C, H, W, K, R, S, stride, pad, flags, csr->nnz, &mp)) {
+    if (mp.total_wgs > 0) {
         const MatrixCall c = {N, C, H, W, K, R, S, stride, pad, a.Ho, a.Wo, (flags & SPCONV_MAXPOOL2X2) != 0,
                               (flags & SPCONV_UNPADDED_INPUT) != 0, a.relu, a.out_pad, a.opitch, a.res_pad, a.rpitch,
                               a.oplane, a.rplane};
@@ -2412,14 +2441,14 @@ extern "C" int spconv_plan(int N, int C, int H, int W, const spconv_csr *csr, in
     if (!info) return SPCONV_EINVAL;
     Plan pl;
     FwdArgs a;
+    MatrixPlan mp;
     int rc = prepare_forward(N, C, H, W, csr, K, R, S, stride, pad, flags, opt ? opt->max_row_nnz : 0,
-                             opt && opt->lowered, &pl, &a);
+                             opt && opt->lowered, &pl, &a, &mp);
     if (rc != SPCONV_OK) return rc;
     rc = apply_epilogue(opt, &a);
     if (rc != SPCONV_OK) return rc;
     const bool s1 = pl.kind == Kind::kStride1;
-    MatrixPlan mp;
-    if (!(opt && opt->lowered) && use_matrix(N, C, H, W, K, R, S, stride, pad, flags, csr->nnz, &mp)) {
+    if (mp.total_wgs > 0) {
         info->kernel = SPCONV_KERNEL_MATRIX;
         info->pixels_per_lane = mp.NBX;
         info->images_per_group = 1;

@@ -551,19 +551,20 @@ class SparseConvLayer:
 
     def can_pad_in_kernel(self, N: int) -> bool:
         """Whether this layer's kernel can form the zero border itself (the
-        dense kernel and stride-1 sparse plans)."""
+        dense kernel and sparse layers of stride 1)."""
         cache = self.__dict__.setdefault("_can_pad_in_kernel", {})
         if N not in cache:
-            cache[N] = self.path == "dense" or self.plan(N)["kernel"] == SPCONV_KERNEL_STRIDE1
+            cache[N] = self.path == "dense" or (self.stride == 1 and self.plan(N)["kernel"] != SPCONV_KERNEL_GENERIC)
         return cache[N]
 
     def pads_in_kernel(self, N: int) -> bool:
         """Whether ``forward`` forms the zero border in the kernel (it can, and
-        that beats a pad pass: always for the dense kernel, for the sparse
-        stride-1 kernel on rows of whole 16-byte groups)."""
+        that beats a pad pass: always for the dense and matrix kernels, which
+        read their input through registers, for the sparse stride-1 kernel on
+        rows of whole 16-byte groups)."""
         if not self.can_pad_in_kernel(N):
             return False
-        return self.path == "dense" or self.W % 4 == 0
+        return self.path == "dense" or self.W % 4 == 0 or self.plan(N)["kernel"] == SPCONV_KERNEL_MATRIX
 
     def forward(self, x, out=None, stream=None, out_pad: int = 0, residual=None, residual_pad: int = 0, xp=None,
                 pad_in_kernel: bool | None = None):

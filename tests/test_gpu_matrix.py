@@ -42,8 +42,8 @@ CASES = [
     (5, 25, 9, 6, 7, 7, 7, 3, 3, 0.05, True, False),
     (8, 8, 29, 96, 77, 1, 1, 2, 0, 0.2, False, False),    # (4, 16)
     (2, 10, 146, 50, 67, 1, 1, 2, 0, 0.2, True, False),
-    (22, 11, 87, 78, 94, 1, 1, 2, 0, 0.13, False, False),  # (4, 32)
-    (34, 14, 84, 65, 66, 1, 1, 2, 0, 0.16, True, False),
+    (14, 8, 214, 62, 53, 1, 1, 2, 0, 0.29, False, False),  # (4, 32)
+    (23, 59, 167, 41, 52, 1, 1, 2, 0, 0.06, True, False),
     (30, 13, 239, 27, 18, 1, 1, 2, 0, 0.06, False, False),  # (7, 16)
     (5, 9, 8, 186, 193, 3, 3, 2, 1, 0.1, True, False),
     (1, 8, 1, 3, 3, 3, 3, 2, 1, 1.0, False, False),       # smallest
@@ -150,3 +150,37 @@ def test_replayed_graph_matches_the_eager_call(sp):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out.view(torch.int32), eager.view(torch.int32))
+
+
+# N, C, K, H, W, R, density, pool: stride-1 layers the planner gives to the matrix kernel
+STRIDE1 = [
+    (8, 128, 128, 28, 28, 3, 0.6, True),
+    (1, 256, 256, 14, 14, 3, 0.3, False),
+    (2, 120, 100, 30, 41, 5, 0.4, False),
+    (3, 200, 203, 20, 23, 3, 0.5, False),
+]
+
+
+@pytest.mark.parametrize("case", STRIDE1)
+def test_stride1_layers(sp, case):
+    """Against the oracle; an unpadded input gives the padded one's bits; a call
+    with a lowered stream still runs the stride-1 kernel; the row hint changes
+    nothing."""
+    import torch
+    N, C, K, H, W, R, d, pool = case
+    layer = synth.random_layer(9700 + H, N, C, K, H, W, R, R, 1, R // 2, d, True, pool, True, False)
+    L, _ = _on_device(sp, layer)
+    x = torch.from_numpy(layer.x).cuda()
+    assert L.pads_in_kernel(N) and L.lowered(N) is None
+    out = L.run(x)
+    raw = L.forward(x)
+    args = (L.pad_input(x), N, C, H, W, L.csr, K, R, R, 1, L.pad, L.bias, L.flags)
+    hinted = sp.spconv_forward(*args)
+    lw = torch.from_numpy(sp.spconv_pack_lowered(L.host_csr, N, H, W, 1, L.pad, L.flags, L.csr.max_row_nnz)).cuda()
+    walked = sp.spconv_forward_ex(*args, lowered=lw)
+    torch.cuda.synchronize()
+    ref, ab = oracle.conv(layer.x, layer.w, layer.mask, layer.bias, 1, layer.pad, True, pool)
+    for what, t in (("matrix", out), ("lowered", walked)):
+        check_close(t.cpu().numpy(), ref, ab, f"{what} {case}")
+    assert torch.equal(out.view(torch.int32), raw.view(torch.int32))
+    assert torch.equal(out.view(torch.int32), hinted.view(torch.int32))
