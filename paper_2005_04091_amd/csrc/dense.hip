@@ -162,7 +162,14 @@ __device__ __forceinline__ float dense_sum_fp32(const float *__restrict__ img, c
 // are two to three times closer than that kernel's (14x14: 1.5e-7 against
 // 4.1e-7 relative), because the hh products round into the main sum once per
 // 16 channels and tap. Chunks of 32 to 96 channels take the same time.
-template <int R, int S, int NBW, bool POOL>
+//
+// PAIR (filters of several taps, at most 8 channels): the second half of an
+// MFMA's 16 channels would be padding, so it takes the next tap instead, 5 MFMA
+// steps for 3x3 where there were 9, and only one octet is staged.
+// 3x3 on 3 channels, 64 outputs, 224x224 batch 32: 396 -> 334 us (fp32 MFMA
+// kernel 388); 56x56 batch 8 10.8 us (14.4); 8 channels at 112x112, batch 4,
+// 16.6 us (32.8). The output's stores are most of what is left.
+template <int R, int S, int NBW, bool POOL, bool PAIR>
 __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs a, const float *__restrict__ xp,
                                                                             const float *__restrict__ wpk,
                                                                             const float *__restrict__ bias,
@@ -170,6 +177,7 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
                                                                             float *__restrict__ out) {
     extern __shared__ float lds[];
     constexpr int RS = R * S;
+    constexpr int T = PAIR ? (RS + 1) / 2 : RS;  // MFMA steps of a channel group
     char *ldsb = reinterpret_cast<char *>(lds);
     const int lane = (int)threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
@@ -207,15 +215,22 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
     const uint32_t wtap = (uint32_t)a.Kp * 8u, wpair = wtap * RS;
     uint32_t wlane[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) wlane[j] = (uint32_t)(k0 + col) * 8u + (uint32_t)(4 * half + j) * wpair;
+    for (int j = 0; j < 4; ++j)
+        wlane[j] = (uint32_t)(k0 + col) * 8u + (uint32_t)(PAIR ? j : 4 * half + j) * wpair + (PAIR ? half * wtap : 0u);
+    // (a group past the last, whose values are not used, reads the first)
     auto a_rsrc = [&](int g) {
-        const int left = max(npairs - 8 * g, 0);
-        return uniform_rsrc(wpk + (size_t)(left ? 8 * g : 0) * (wpair / 4), (uint32_t)min(left, 8) * wpair);
+        const int g0 = 8 * g < npairs ? 8 * g : 0;
+        return uniform_rsrc(wpk + (size_t)g0 * (wpair / 4), (uint32_t)min(npairs - g0, 8) * wpair);
     };
+    // A fragment of step t; with PAIR taps 2t and 2t + 1, zeros past the last
+    // tap (an offset past any range: the packed filter is below 2^31 bytes).
     auto load_a = [&](f32x2_t(&av)[4], const __amdgpu_buffer_rsrc_t &rs, int t) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            av[j] = __builtin_bit_cast(f32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rs, wlane[j], t * wtap, 0));
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t v = PAIR && 2 * t + 1 >= RS && half ? 0x7ffffff0u : wlane[j];
+            av[j] = __builtin_bit_cast(f32x2_t,
+                                       __builtin_amdgcn_raw_buffer_load_b64(rs, v, (PAIR ? 2 * t : t) * wtap, 0));
+        }
     };
 
     StageTask task[kDnsRounds];
@@ -251,7 +266,7 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
 
     stage_load(0);
     const int ngroups = (a.C + kDnsGroup - 1) / kDnsGroup;
-    const int lane_b = (half * a.PX + q0 + col) * 16;
+    const int lane_b = ((PAIR ? 0 : half * a.PX) + q0 + col) * 16;
     // Steps of this wave: (group, tap), groups wr, wr + ksr, ... over all
     // chunks. A wave runs them as one pipeline: the A loads three steps ahead,
     // the split of the next step's A and the B reads of the next unit (one
@@ -260,8 +275,8 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
     Parts A;
     if (active) {
         load_a(araw[0], a_rsrc(wr), 0);
-        load_a(araw[1], a_rsrc(wr + 1 / RS * a.ksr), 1 % RS);
-        load_a(araw[2], a_rsrc(wr + 2 / RS * a.ksr), 2 % RS);
+        load_a(araw[1], a_rsrc(wr + 1 / T * a.ksr), 1 % T);
+        load_a(araw[2], a_rsrc(wr + 2 / T * a.ksr), 2 % T);
     }
     stage_put(0, ldsb);
     if (active)
@@ -284,29 +299,35 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
                                                     0, 0, 0);
     };
 
+    // B bytes from the lane's pixel to the pixel under step t's tap.
+    auto tap_at = [&](int t) {
+        if constexpr (!PAIR) return ((t / S) * a.Wp + t % S) * 16;
+        const int t0 = 2 * t, t1 = min(2 * t + 1, RS - 1);  // (past the last tap: the last, times zeros)
+        return (half ? (t1 / S) * a.Wp + t1 % S : (t0 / S) * a.Wp + t0 % S) * 16;
+    };
     for (int ch = 0; ch < a.nchunks; ++ch) {
-        const bool more = ch + 1 < a.nchunks;
+        const bool more = !PAIR && ch + 1 < a.nchunks;  // (one group is one chunk)
         if (more) stage_load(ch + 1);
         const char *buf = ldsb + (a.nbuf == 2 ? (ch & 1) * a.buf_bytes : 0) + lane_b;
         const int gn = min(a.Cg, ngroups - ch * a.Cg);
         const int gstride = a.PX * kDnsPxBytes;
         if (active && wr < gn) {
             Parts B[2];
-            read_b(B[0], buf + wr * gstride, 0);
+            read_b(B[0], buf + wr * gstride + tap_at(0), 0);
             for (int g = wr; g < gn; g += a.ksr) {
                 const char *gb = buf + g * gstride;
                 const char *gnext = g + a.ksr < gn ? gb + a.ksr * gstride : gb;  // (the last group's reads repeat)
                 const int gg = ch * a.Cg + g;
-                const __amdgpu_buffer_rsrc_t rs0 = a_rsrc(gg), rs1 = a_rsrc(gg + (RS == 1 ? 3 : 1) * a.ksr);
+                const __amdgpu_buffer_rsrc_t rs0 = a_rsrc(gg), rs1 = a_rsrc(gg + (T == 1 ? 3 : 1) * a.ksr);
 #pragma unroll
-                for (int t = 0; t < RS; ++t) {
+                for (int t = 0; t < T; ++t) {
                     // araw[t % 3] is split already: its registers take step t + 3.
-                    load_a(araw[t % 3], t + 3 < RS ? rs0 : rs1, (t + 3) % RS);
+                    if (!PAIR || t + 3 < T) load_a(araw[t % 3], t + 3 < T ? rs0 : rs1, (t + 3) % T);
                     Parts An;
 #pragma unroll
                     for (int b = 0; b < NBW; ++b) {
                         const int un = t * NBW + b, tn = (un + 1) / NBW, bn = (un + 1) % NBW;
-                        read_b(B[(un + 1) & 1], tn < RS ? gb + ((tn / S) * a.Wp + tn % S) * 16 : gnext, bn);
+                        read_b(B[(un + 1) & 1], tn < T ? gb + tap_at(tn) : gnext, bn);
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
                             if (j * NBW / 4 == b) {  // the split's four pairs, dealt to the units
@@ -323,7 +344,8 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
                         mma(acc[b], A.h, Bu.h);
                         if constexpr (RS > 1) {
                             __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);              // LDS reads
-                            if (b == 0) __builtin_amdgcn_sched_group_barrier(0x020, 4, 0);  // A loads
+                            if (b == 0 && (!PAIR || t + 3 < T))
+                                __builtin_amdgcn_sched_group_barrier(0x020, 4, 0);  // A loads
 #pragma unroll
                             for (int k = 0; k < 6; ++k) {
                                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
@@ -334,8 +356,8 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
                     }
                     A = An;
                 }
-                if constexpr ((RS * NBW) % 2 == 1) B[0] = B[1];
-                if constexpr (RS % 3 != 0) {  // one tap: the ring turns by copies
+                if constexpr ((T * NBW) % 2 == 1) B[0] = B[1];
+                if constexpr (T % 3 != 0 && !PAIR) {  // one tap: the ring turns by copies
                     static_assert(RS == 1, "filters of the dense kernel");
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
@@ -520,26 +542,30 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
 
 using DenseKernel = void (*)(DenseArgs, const float *, const float *, const float *, const float *, float *);
 
-template <int R, int S, int NBW>
+template <int R, int S, int NBW, bool PAIR>
 DenseKernel pick_dense_pool(bool pool) {
-    return pool ? spconv_dense_kernel<R, S, NBW, true> : spconv_dense_kernel<R, S, NBW, false>;
+    return pool ? spconv_dense_kernel<R, S, NBW, true, PAIR> : spconv_dense_kernel<R, S, NBW, false, PAIR>;
 }
 
-template <int R, int S>
+template <int R, int S, bool PAIR>
 DenseKernel pick_dense_nbw(int NBW, bool pool) {
     switch (NBW) {
-        case 1: return pick_dense_pool<R, S, 1>(pool);
-        case 2: return pick_dense_pool<R, S, 2>(pool);
-        case 3: return pick_dense_pool<R, S, 3>(pool);
-        case 4: return pick_dense_pool<R, S, kDnsWaveBlocks>(pool);
+        case 1: return pick_dense_pool<R, S, 1, PAIR>(pool);
+        case 2: return pick_dense_pool<R, S, 2, PAIR>(pool);
+        case 3: return pick_dense_pool<R, S, 3, PAIR>(pool);
+        case 4: return pick_dense_pool<R, S, kDnsWaveBlocks, PAIR>(pool);
         default: return nullptr;
     }
 }
 
+// Two taps per MFMA step: one octet of channels, several taps.
+bool dense_pairs(int C, int R, int S) { return C <= 8 && R * S > 1; }
+
 // Filter shapes the dense kernel is built for.
-DenseKernel pick_dense(int R, int S, int NBW, bool pool) {
-    if (R == 3 && S == 3) return pick_dense_nbw<3, 3>(NBW, pool);
-    if (R == 1 && S == 1) return pick_dense_nbw<1, 1>(NBW, pool);
+DenseKernel pick_dense(int C, int R, int S, int NBW, bool pool) {
+    if (R == 3 && S == 3)
+        return dense_pairs(C, R, S) ? pick_dense_nbw<3, 3, true>(NBW, pool) : pick_dense_nbw<3, 3, false>(NBW, pool);
+    if (R == 1 && S == 1) return pick_dense_nbw<1, 1, false>(NBW, pool);
     return nullptr;
 }
 
@@ -704,7 +730,7 @@ int prepare_dense(int N, int C, int H, int W, int K, int R, int S, int pad, uint
     if (pool && (Ho < 2 || Wo < 2)) return SPCONV_EINVAL;
     DensePlan pl;
     if (!plan_dense(N, C, K, H, W, pad, (int)Wp, Ho, Wo, R, S, pool, &pl)) return SPCONV_EINVAL;
-    if (!pick_dense(R, S, pl.NBW, pool)) return SPCONV_EINVAL;
+    if (!pick_dense(C, R, S, pl.NBW, pool)) return SPCONV_EINVAL;
     DenseArgs a;
     a.N = N;
     a.C = C;
@@ -740,7 +766,7 @@ int prepare_dense(int N, int C, int H, int W, int K, int R, int S, int pad, uint
     a.nchunks = pl.nchunks;
     a.nbuf = pl.nbuf;
     a.PX = pl.PX;
-    a.tasks = 2 * pl.Cg * pl.PX;
+    a.tasks = (dense_pairs(C, R, S) ? 1 : 2 * pl.Cg) * pl.PX;
     a.buf_bytes = pl.Cg * pl.PX * kDnsPxBytes;
     if (!div_magic((uint32_t)pl.PX, &a.px_magic, &a.px_shift)) return SPCONV_EINVAL;
     a.total_wgs = pl.total_wgs;
@@ -771,7 +797,7 @@ extern "C" int spconv_forward_dense(const float *in_padded, int N, int C, int H,
     DenseArgs a;
     const int rc = prepare_dense(N, C, H, W, K, R, S, pad, flags, opt, &pl, &a);
     if (rc != SPCONV_OK) return rc;
-    DenseKernel kern = pick_dense(R, S, pl.NBW, (flags & SPCONV_MAXPOOL2X2) != 0);
+    DenseKernel kern = pick_dense(C, R, S, pl.NBW, (flags & SPCONV_MAXPOOL2X2) != 0);
     const float *residual = opt ? opt->residual : nullptr;
     // Raised once per instance to the family's budget (see raise_lds_limit).
     if (!raise_lds_limit((const void *)kern, kDnsLdsMax)) return SPCONV_EHIP;

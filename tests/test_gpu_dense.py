@@ -197,3 +197,33 @@ def test_dense_extreme_values(sp):
     assert np.array_equal(np.isinf(got) & (ab < 1e38), np.isinf(ref) & (ab < 1e38))
     fin = np.isfinite(ref) & (ab < 3e38)
     assert (np.abs(got[fin] - ref[fin]) <= REL_TOL * ab[fin] + ABS_TOL).all()
+
+
+@pytest.mark.parametrize("C", [1, 3, 8])
+@pytest.mark.parametrize("H,W,pool", [(5, 7, False), (17, 62, True), (4, 222, False), (12, 94, True)])
+def test_dense_tap_pairs(sp, C, H, W, pool):
+    """At most 8 channels: two taps to a matrix step (one to eight pixel blocks),
+    against the oracle and with an infinite and a NaN input next to finite ones."""
+    import torch
+    layer = synth.random_layer(8300 + C, 2, C, 40, H, W, 3, 3, 1, 1, 0.8, False, pool, True, False)
+    layer.w[:] = np.where(layer.w == 0, 0.25, layer.w)
+    L = sp.SparseConvLayer(layer.w, None, layer.bias, H, W, 1, 1, False, pool, path="dense")
+    say("dense tap pairs", C, H, W, pool, L.plan(2))
+    x = torch.from_numpy(layer.x).cuda()
+    out = L.run(x)
+    padded = L.forward_padded(L.pad_input(x))
+    bad = x.clone()
+    bad[0, C - 1, 2, 3] = float("inf")
+    bad[1, 0, 4 if H > 4 else 3, W - 1] = float("nan")
+    raw = L.run(bad)
+    torch.cuda.synchronize()
+    ref, ab = oracle.conv(layer.x, layer.w, None, layer.bias, 1, 1, False, pool)
+    check_close(out.cpu().numpy(), ref, ab, f"tap pairs {C} {H}x{W}")
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), padded.cpu().numpy().view(np.uint32))
+    conv = torch.nn.functional.conv2d(bad.cpu().double(), torch.from_numpy(layer.w).double(),
+                                      torch.from_numpy(layer.bias).double(), padding=1)
+    if not pool:
+        got, want = raw.cpu().double(), conv
+        assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(torch.isinf(got), torch.isinf(want))
+        same = torch.isfinite(want)
+        assert torch.equal(got[same], out.cpu().double()[same])
