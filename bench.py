@@ -33,7 +33,8 @@ sys.path.insert(0, str(ROOT))
 
 HBM_PEAK_GBS = 8000.0           # MI355X HBM3E, published
 VALU_FP32_FMA_TFLOPS = 78.6     # 256 CU x 64 lanes x 2 FLOP x 2.4 GHz (v_fma_f32; packed FP32 forms not used)
-MFMA_FP32_TFLOPS = 157.3        # MI355X dense fp32 matrix peak, published
+# fp32 products on the bf16 matrix cores: six part products each, of the published dense bf16 peak
+MFMA_SPLIT_FP32_TFLOPS = round(2500.0 / 6, 1)
 FP32_VECTOR_PUBLISHED_TFLOPS = 157.3
 
 WORKLOADS = {
@@ -88,7 +89,7 @@ def algorithmic(layer, nnz):
 # (profiles/spconv_<family>_<workload>_traffic.json).
 KERNEL_SOURCES = {
     "fwd": [ROOT / "paper_2005_04091_amd" / "csrc" / f for f in ("spconv.hip", "common.h")],
-    "dense": [ROOT / "paper_2005_04091_amd" / "csrc" / f for f in ("dense.hip", "common.h")],
+    "dense": [ROOT / "paper_2005_04091_amd" / "csrc" / f for f in ("dense.hip", "split.h", "common.h")],
 }
 
 
@@ -446,7 +447,7 @@ def per_config_record(name, args, dev, stream):
     back-to-back launches (warm), the cold median of 30 of the forward alone and
     of pad + forward, nonzero GFLOP/s, and the roofline figures against HBM and
     the arithmetic peak of the path that runs (v_fma_f32 for the sparse kernels,
-    the fp32 matrix cores for the dense one)."""
+    fp32 products as six bf16 part products on the matrix cores for the dense one)."""
     import torch
     from paper_2005_04091_amd import spconv, synth
     layer = synth.make_layer(name)
@@ -484,8 +485,8 @@ def per_config_record(name, args, dev, stream):
     if L.path == "dense":
         dflops = 2.0 * K * C * R * S * N * L.Ho * L.Wo
         nbytes_d = nbytes + 4.0 * L.dense.numel() - 8.0 * nnz
-        rec["roof"] = roof(dflops, nbytes_d, ms_cold, MFMA_FP32_TFLOPS)
-        rec["roof"]["flops_counted"] = "dense filter work on the fp32 matrix cores"
+        rec["roof"] = roof(dflops, nbytes_d, ms_cold, MFMA_SPLIT_FP32_TFLOPS)
+        rec["roof"]["flops_counted"] = "dense filter work, six bf16 part products per fp32 product"
         rec["nonzero_flops_roof"] = roof(flops, nbytes, ms_cold, VALU_FP32_FMA_TFLOPS)
     else:
         rec["roof"] = roof(flops, nbytes, ms_cold, VALU_FP32_FMA_TFLOPS)
@@ -821,11 +822,11 @@ def main():
     value = flops / (ms_per_step * 1e-3) / 1e9
     if dense:
         # The dense kernel's algorithmic work is every filter tap (its FLOPs on
-        # the stored pixels), on the fp32 matrix cores; its filter read is the
+        # the stored pixels), as bf16 part products; its filter read is the
         # packed dense array instead of the CSR.
         kern_flops = 2.0 * K * C * R * S * N * (H + 2 * layer.pad - R + 1) * (W + 2 * layer.pad - S + 1)
         fwd_bytes += 4.0 * L.dense.numel() - (8.0 * nnz)
-        bound, peak, kname = "mfma", MFMA_FP32_TFLOPS, "spconv_dense_kernel"
+        bound, peak, kname = "mfma", MFMA_SPLIT_FP32_TFLOPS, "spconv_dense_kernel"
     else:
         kern_flops = flops
         bound, peak, kname = "alu", VALU_FP32_FMA_TFLOPS, "spconv_fwd_kernel"

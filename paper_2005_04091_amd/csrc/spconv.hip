@@ -27,8 +27,11 @@
 //  * accumulators stay in VGPRs across the chunks; the epilogue adds the bias,
 //    applies ReLU and, for the pooled variant, reduces 2x2 windows through an
 //    LDS staging tile before the single store.
-// MFMA is not used: at the densities this path serves, the work is a
-// gather-accumulate, not a dense contraction.
+// This file's kernels use no MFMA: at the densities they serve, the work is a
+// gather-accumulate, not a dense contraction. Calls without a lowered stream
+// whose filters are dense enough, or whose stride is not 1, run in matrix.hip
+// (use_matrix below states the rule); the any-stride kernel here is left with
+// strided layers of fewer than 8 input channels.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1529,7 +1532,7 @@ __global__ __launch_bounds__(kS1Threads) __attribute__((amdgpu_waves_per_eu(4, 4
     s1_epilogue<PI, IPW, RPW, POOL>(a, accE, accO, krow, ig, ty, y0, 0, wave, lane, lds, lds, bias, res, out);
 }
 
-// Generic-stride kernel: waves split the pixels of the tile and every wave
+// Generic-stride kernel (strided layers of fewer than 8 channels): waves split the pixels of the tile and every wave
 // walks all KT rows; each pixel keeps its own LDS base (y*stride*Wp +
 // x*stride), so a nonzero costs one address add per pixel. Correct for any
 // stride; the stride-1 kernel above is the fast path.
