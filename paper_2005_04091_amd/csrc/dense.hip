@@ -166,8 +166,8 @@ __device__ __forceinline__ float dense_sum_fp32(const float *__restrict__ img, c
 // PAIR (filters of several taps, at most 8 channels): the second half of an
 // MFMA's 16 channels would be padding, so it takes the next tap instead, 5 MFMA
 // steps for 3x3 where there were 9, and only one octet is staged.
-// 3x3 on 3 channels, 64 outputs, 224x224 batch 32: 396 -> 334 us (fp32 MFMA
-// kernel 388); 56x56 batch 8 10.8 us (14.4); 8 channels at 112x112, batch 4,
+// 3x3 on 3 channels, 64 outputs, 224x224 batch 32: 396 -> 321 us (fp32 MFMA
+// kernel 374); 56x56 batch 8 10.8 us (14.4); 8 channels at 112x112, batch 4,
 // 16.6 us (32.8). The output's stores are most of what is left.
 template <int R, int S, int NBW, bool POOL, bool PAIR>
 __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs a, const float *__restrict__ xp,

@@ -1,4 +1,4 @@
-"""GPU parity of the dense path (spconv_forward_dense, fp32 MFMA) against the
+"""GPU parity of the dense path (spconv_forward_dense, fp32 products on the matrix cores) against the
 oracle, with the layer tolerance 1e-5 * sum|w*x| + 1e-6 per output (both paths
 accumulate in fp32; only the order differs). Cases cover one to four waves per
 workgroup, several channel tiles, partial channel tiles (K not a multiple of
