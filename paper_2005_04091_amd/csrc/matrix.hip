@@ -595,6 +595,9 @@ bool search_plan(int N, int C, int H, int W, int K, int R, int S, int stride, in
     if (plane >= (1 << 24) || C >= (1 << 24) || W + 2LL * pad < 2) return false;
     const int Hp = H + 2 * pad, Wp = W + 2 * pad;
     const int Ho = (Hp - R) / stride + 1, Wo = (Wp - S) / stride + 1;
+    // One output row (column) reads the window of one position, however far the
+    // next would be: a stride past the plane would be a window pitch past any LDS.
+    const int sy = Ho > 1 ? stride : 1, sx = Wo > 1 ? stride : 1;
     const int taps = R * S;
     const int noct = ceil_div(C, 8);
     const double per_row_chan = (double)nnz / K / C;  // entries per (row, channel)
@@ -628,8 +631,8 @@ bool search_plan(int N, int C, int H, int W, int K, int R, int S, int stride, in
                     int TH = ceil_div(Ho, nty);
                     if (pool && (TH & 1)) ++TH;
                     const int nx = ceil_div(Wo, TW), ny = ceil_div(Ho, TH);
-                    const int stepy = R == 1 ? stride : 1, stepx = S == 1 ? stride : 1;
-                    const int lsy = R == 1 ? 1 : stride, lsx = S == 1 ? 1 : stride;
+                    const int stepy = R == 1 ? sy : 1, stepx = S == 1 ? sx : 1;
+                    const int lsy = R == 1 ? 1 : sy, lsx = S == 1 ? 1 : sx;
                     const int rows = (TH - 1) * lsy + R, hw = ceil_div((TW - 1) * lsx + S, lsx), vp = lsx * hw;
                     const int PX = rows * vp;
                     for (int O : {16, 8, 4, 2, 1}) {

@@ -184,3 +184,17 @@ def test_stride1_layers(sp, case):
         check_close(t.cpu().numpy(), ref, ab, f"{what} {case}")
     assert torch.equal(out.view(torch.int32), raw.view(torch.int32))
     assert torch.equal(out.view(torch.int32), hinted.view(torch.int32))
+
+
+@pytest.mark.parametrize("stride", [7, 1431655766, (1 << 31) - 1])
+@pytest.mark.parametrize("C,H,W,R,S", [(8, 3, 3, 3, 3), (17, 5, 4, 5, 3), (16, 4, 6, 1, 3)])
+def test_strides_past_the_plane(sp, stride, C, H, W, R, S):
+    """One output pixel per image, against the oracle."""
+    import torch
+    layer = synth.random_layer(9800 + C, 3, C, 21, H, W, R, S, stride, 0, 0.4, True, False, True, False)
+    L, plan = _on_device(sp, layer)
+    assert (L.Ho, L.Wo, plan["tile_pixels"]) == (1, 1, 1)
+    out = L.forward_padded(L.pad_input(torch.from_numpy(layer.x).cuda()))
+    torch.cuda.synchronize()
+    ref, ab = oracle.conv(layer.x, layer.w, layer.mask, layer.bias, stride, 0, True, False)
+    check_close(out.cpu().numpy(), ref, ab, f"stride {stride}")

@@ -1,0 +1,27 @@
+"""CPU tests of the matrix kernel's host side: the launch plans of strided
+layers (and of the stride-1 layers that kernel takes) as spconv_plan reports
+them. Nothing is queued on a GPU."""
+import pytest
+
+
+@pytest.fixture(scope="module")
+def sp():
+    from paper_2005_04091_amd import spconv
+    return spconv
+
+
+def plan(sp, N, C, K, H, W, R, S, stride, pad, nnz, flags=1, **kw):
+    csr = sp.spconv_csr(K, C, R, S, H + 2 * pad, W + 2 * pad, nnz, 16, 16, 16, 16)
+    return sp.spconv_plan(N, C, H, W, csr, K, R, S, stride, pad, flags, **kw)
+
+
+@pytest.mark.parametrize("C,H,W,R,S", [(8, 3, 3, 3, 3), (16, 4, 4, 3, 3), (16, 5, 5, 5, 5), (16, 4, 40, 3, 1),
+                                       (24, 40, 4, 1, 3), (9, 6, 6, 1, 1)])
+@pytest.mark.parametrize("stride", [100, 1 << 20, 858993460, 1431655765, 1431655766, 1431655767, (1 << 31) - 1])
+def test_a_stride_past_the_plane_is_any_stride_past_it(sp, C, H, W, R, S, stride):
+    """One output pixel: the staged window is the filter's, whatever the stride
+    (rows and columns a stride apart would be billions of LDS pixels)."""
+    K = 20
+    p = plan(sp, 1, C, K, H, W, R, S, stride, 0, K * C)
+    assert p == plan(sp, 1, C, K, H, W, R, S, max(H, W), 0, K * C)
+    assert p["kernel"] == sp.SPCONV_KERNEL_MATRIX and p["tile_pixels"] == 1
