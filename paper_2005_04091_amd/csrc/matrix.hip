@@ -245,13 +245,18 @@ __global__ __launch_bounds__(kMatThreads) void spconv_matrix_kernel(MatArgs a, c
     };
     // Filter fragments of chunk ch: a row's lanes clear its slots and store its
     // entries there (no other wave touches them, and a wave's LDS operations
-    // run in order), from the queue loaded before, then the queue moves on.
+    // run in order), from the queue loaded before, then the queue moves on. A
+    // lane's entries fall in slots that another lane cleared, which neither its
+    // own addresses nor the types tell the compiler: the wavefront fence, no
+    // instruction, keeps the clears first.
     auto put_a = [&](char *buf, int ch) __attribute__((always_inline)) {
         const int c0 = ch * a.O * 8;
         const int bound = min(c0 + a.O * 8, a.C) * a.plane;
         for (int s = sub; s < a.nunits * 12; s += lpr)  // slot s: (unit, part, quarter)
             *reinterpret_cast<u32x4_t *>(buf + fbase + s * 256 + ((frow + s) & 15) * 16) =
                 (u32x4_t){0u, 0u, 0u, 0u};
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
         int got = 0;
 #pragma unroll
         for (int i = 0; i < kMatQueue; ++i)
