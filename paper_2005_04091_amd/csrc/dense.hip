@@ -801,9 +801,20 @@ extern "C" int spconv_forward_dense(const float *in_padded, int N, int C, int H,
     const float *residual = opt ? opt->residual : nullptr;
     // Raised once per instance to the family's budget (see raise_lds_limit).
     if (!raise_lds_limit((const void *)kern, kDnsLdsMax)) return SPCONV_EHIP;
-    hipLaunchKernelGGL(kern, dim3((unsigned)pl.total_wgs), dim3((unsigned)(pl.nw * pl.ksr * pl.ksp * kWave)), pl.lds_bytes, stream, a,
-                       in_padded, packed, bias, residual, out);
-    return hipGetLastError() == hipSuccess ? SPCONV_OK : SPCONV_EHIP;
+    // A launch counts its threads in 32 bits: tens of millions of images take
+    // several, each of as many whole images as fit.
+    const int threads = pl.nw * pl.ksr * pl.ksp * kWave, per_image = pl.total_wgs / N;
+    const int most = (int)std::min<long long>(N, std::max(1LL, 0xffffffffLL / threads / per_image));
+    for (int n0 = 0; n0 < N; n0 += most) {
+        a.N = std::min(most, N - n0);
+        a.total_wgs = a.N * per_image;
+        hipLaunchKernelGGL(kern, dim3((unsigned)a.total_wgs), dim3((unsigned)threads), pl.lds_bytes, stream, a,
+                           in_padded + (size_t)n0 * C * a.IH * a.IW, packed, bias,
+                           residual ? residual + (size_t)n0 * K * a.rplane : nullptr, out + (size_t)n0 * K * a.oplane);
+        if (hipGetLastError() != hipSuccess) return SPCONV_EHIP;
+        if (N - n0 <= most) break;  // (n0 + most may pass int)
+    }
+    return SPCONV_OK;
 }
 
 extern "C" int spconv_dense_plan(int N, int C, int H, int W, int K, int R, int S, int pad, uint32_t flags,

@@ -651,7 +651,9 @@ bool search_plan(int N, int C, int H, int W, int K, int R, int S, int stride, in
                         const int bufs = nchunks > 1 && 2 * (a_bytes + b_bytes) + tab <= kMatLdsBytes ? 2 : 1;
                         if ((long long)O * 8 * Hp * Wp * 4 >= (1LL << 31)) continue;
                         const long long wgs = (long long)N * nx * ny * ceil_div(K, M);
-                        if (wgs > 0x7fffffffLL) continue;
+                        // A launch counts its threads in 32 bits (the other kernels hold
+                        // several small images in a workgroup, and so reach further).
+                        if (wgs * kMatThreads >= (1LL << 32)) continue;
                         const size_t lds = std::max((size_t)(bufs * (a_bytes + b_bytes) + tab), epi);
                         const double units = (double)nchunks * nunits / ksr;
                         const double mfma = 2.0 * units * RB * NBX * 6 * 20;

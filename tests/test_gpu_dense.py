@@ -227,3 +227,23 @@ def test_dense_tap_pairs(sp, C, H, W, pool):
         assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(torch.isinf(got), torch.isinf(want))
         same = torch.isfinite(want)
         assert torch.equal(got[same], out.cpu().double()[same])
+
+
+def test_dense_more_images_than_one_launch_counts(sp):
+    """34 million images of 3x3 on 128 threads each pass the 2^32 threads of one
+    launch: every image against the same image in calls of a million (bit for bit)."""
+    import torch
+    N, part = 34_000_000, 1_000_000
+    layer = synth.random_layer(8400, 1, 1, 1, 3, 3, 3, 3, 1, 1, 1.0, True, False, True, False)
+    L = _dense_layer(sp, layer)
+    p = L.plan(N)
+    assert p["launch_workgroups"] * p["threads_per_workgroup"] >= 1 << 32
+    say("dense many images", p)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randn((N, 1, 3, 3), generator=g, device="cuda")
+    out = L.forward(x)
+    for n in range(0, N, part):
+        assert torch.equal(out[n:n + part], L.forward(x[n:n + part]))
+    torch.cuda.synchronize()
+    del x, out
+    torch.cuda.empty_cache()

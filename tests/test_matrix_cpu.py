@@ -25,3 +25,15 @@ def test_a_stride_past_the_plane_is_any_stride_past_it(sp, C, H, W, R, S, stride
     p = plan(sp, 1, C, K, H, W, R, S, stride, 0, K * C)
     assert p == plan(sp, 1, C, K, H, W, R, S, max(H, W), 0, K * C)
     assert p["kernel"] == sp.SPCONV_KERNEL_MATRIX and p["tile_pixels"] == 1
+
+
+def test_grids_of_many_small_images_stay_below_2_32_threads(sp):
+    """A launch counts its threads in 32 bits. Twelve million 3x3 images, one to a
+    512-thread workgroup, pass them where the any-stride kernel, with several
+    images to a workgroup, does not."""
+    p = plan(sp, 12_000_000, 8, 16, 3, 3, 3, 3, 2, 1, 640)
+    assert p["kernel"] == sp.SPCONV_KERNEL_GENERIC
+    assert p["workgroups"] * p["threads_per_workgroup"] < 1 << 32
+    p = plan(sp, 8_000_000, 8, 16, 3, 3, 3, 3, 2, 1, 640)
+    assert p["kernel"] == sp.SPCONV_KERNEL_MATRIX
+    assert p["workgroups"] * p["threads_per_workgroup"] < 1 << 32
