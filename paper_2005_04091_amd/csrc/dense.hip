@@ -24,9 +24,10 @@
 //  * the A fragment of (group, tap) is four 8-byte loads from the filter
 //    packed by spconv_pack_dense, two steps ahead, split in registers;
 //  * the epilogue adds bias (and a residual), applies ReLU, pools 2x2 windows
-//    through LDS when asked, and stores once. An output that came out NaN is
-//    summed again in plain fp32: infinities (and values that round to one in
-//    bf16) have no finite parts.
+//    through LDS when asked, and stores once. Outputs that are not finite are
+//    summed again in plain fp32: infinities (and values that round to one in bf16)
+//    have no finite parts, and near the top of the range h rounds up past the
+//    value, so that hh can overflow where the product does not.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -138,7 +139,7 @@ __device__ __forceinline__ void dense_put(const DenseArgs &a, char *buf, const S
     *reinterpret_cast<u32x4_t *>(d + a.PX * 64) = p.l;
 }
 
-// Plain fp32 sum of one output, for results that came out NaN.
+// Plain fp32 sum of one output, for results that are not finite.
 template <int R, int S>
 __device__ __forceinline__ float dense_sum_fp32(const float *__restrict__ img, const float *__restrict__ wk,
                                                           int C, int Kp, int IH, int IW, int y, int x) {
@@ -419,13 +420,13 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
         ys[b] = in ? y0 + yl : -1;
         xs[b] = x;
     }
-    // NaN sums of stored outputs are taken again in fp32 (see the file comment).
+    // Stored sums that are not finite are taken again in fp32 (see the file comment).
     uint64_t redo = 0;
 #pragma unroll
     for (int b = 0; b < NBW; ++b)
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj)
-            if (jj < J && ys[b] >= 0 && chan(jj) < a.K && acc[b][jj] != acc[b][jj]) redo |= 1ull << (b * 16 + jj);
+            if (jj < J && ys[b] >= 0 && chan(jj) < a.K && !(fabsf(acc[b][jj]) < INFINITY)) redo |= 1ull << (b * 16 + jj);
     if (__builtin_amdgcn_ballot_w64(redo != 0)) {
         const float *img = xp + (size_t)n * a.C * a.IH * a.IW;
         while (redo) {

@@ -17,8 +17,10 @@
 // no padded columns, and strides only change the bases. Six part products per
 // unit give fp32 products (split.h); the hh products and the smaller ones have
 // separate fp32 sums, so the main sum rounds once per unit.
-// An output that came out NaN is summed again from its CSR entries in fp32
-// (infinities have no finite parts, and zeros of the tile do not count).
+// An output that came out infinite or NaN is summed again from its CSR entries in
+// fp32: infinities have no finite parts, zeros of the tile do not count, and near
+// the top of the range h rounds up past the value, so that hh can overflow where
+// the product does not.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -128,7 +130,7 @@ __device__ __forceinline__ void mat_put(char *buf, const MatTask &t, const float
     *reinterpret_cast<u32x4_t *>(d + 32) = p.l;
 }
 
-// Plain fp32 sum of one output from its CSR row, for results that came out NaN.
+// Plain fp32 sum of one output from its CSR row, for results that are not finite.
 __device__ float mat_sum_fp32(const MatArgs &a, const float *__restrict__ img, const int32_t *__restrict__ offset,
                               const float *__restrict__ vals, int j, int e, int y, int x) {
     float s = 0.0f;
@@ -458,7 +460,7 @@ __global__ __launch_bounds__(kMatThreads) void spconv_matrix_kernel(MatArgs a, c
         for (int b = 0; b < NBX; ++b)
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj)
-                if (jj < J && ys[b] >= 0 && chan(rb, jj) < a.K && acc[rb][b][jj] != acc[rb][b][jj])
+                if (jj < J && ys[b] >= 0 && chan(rb, jj) < a.K && !(fabsf(acc[rb][b][jj]) < INFINITY))
                     redo |= 1ull << ((rb * NBX + b) * 4 + jj);
     if (__builtin_amdgcn_ballot_w64(redo != 0)) {
         const float *img = xp + (size_t)n * a.C * iplane;

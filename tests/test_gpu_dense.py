@@ -247,3 +247,28 @@ def test_dense_more_images_than_one_launch_counts(sp):
     torch.cuda.synchronize()
     del x, out
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("C,K,H,W,pool", [(24, 40, 12, 13, False), (24, 72, 28, 30, True), (5, 40, 9, 30, False),
+                                          (64, 33, 7, 7, False)])
+def test_dense_results_near_the_top_of_the_range(sp, C, K, H, W, pool):
+    """1.7e38 * 2 is finite; its bf16 part rounds up to 2^127, whose product with 2 is not."""
+    import torch
+    layer = synth.random_layer(8500 + C, 2, C, K, H, W, 3, 3, 1, 1, 1.0, False, pool, True, False)
+    layer.w[:, 3, 1, 1] = 2.0
+    layer.x[0, 3, 4, 5] = 1.7e38
+    layer.x[1, 3, 2, 2] = -1.7e38
+    layer.x[1, 3, 6, 6] = 3.4028e38  # rounds to infinity in bf16
+    layer.w[0, 3, 1, 1] = 0.99
+    L = sp.SparseConvLayer(layer.w, None, layer.bias, H, W, 1, 1, False, pool, path="dense")
+    say("dense top of the range", L.plan(2))
+    out = L.run(torch.from_numpy(layer.x).cuda())
+    torch.cuda.synchronize()
+    ref, ab = oracle.conv(layer.x, layer.w, None, layer.bias, 1, 1, False, pool)
+    assert (np.abs(ref) > 3.3e38).any()
+    with np.errstate(over="ignore"):
+        want = ref.astype(np.float32).astype(np.float64)  # infinite where the sum is
+    got = out.cpu().numpy().astype(np.float64)
+    assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    fin = np.isfinite(want)
+    assert (np.abs(got[fin] - want[fin]) <= REL_TOL * ab[fin] + ABS_TOL).all()

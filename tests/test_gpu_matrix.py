@@ -198,3 +198,29 @@ def test_strides_past_the_plane(sp, stride, C, H, W, R, S):
     torch.cuda.synchronize()
     ref, ab = oracle.conv(layer.x, layer.w, layer.mask, layer.bias, stride, 0, True, False)
     check_close(out.cpu().numpy(), ref, ab, f"stride {stride}")
+
+
+def test_results_near_the_top_of_the_range(sp):
+    """1.7e38 * 2 is finite; its bf16 part rounds up to 2^127, whose product with 2
+    is not. A value that rounds to infinity in bf16, times 0.99, is finite too."""
+    import torch
+    for pool in (False, True):
+        layer = synth.random_layer(9900, 2, 24, 40, 21, 23, 3, 3, 2, 1, 0.3, False, pool, True, False)
+        layer.mask[:, 3, 1, 1] = 1
+        layer.w[:, 3, 1, 1] = 2.0
+        layer.w[0, 3, 1, 1] = 0.99
+        layer.x[0, 3, 4, 6] = 1.7e38
+        layer.x[1, 3, 2, 2] = -1.7e38
+        layer.x[1, 3, 6, 6] = 3.4028e38
+        L, _ = _on_device(sp, layer)
+        L.flags &= ~sp.SPCONV_RELU
+        out = L.forward_padded(L.pad_input(torch.from_numpy(layer.x).cuda()))
+        torch.cuda.synchronize()
+        ref, ab = oracle.conv(layer.x, layer.w, layer.mask, layer.bias, 2, 1, False, pool)
+        with np.errstate(over="ignore"):
+            want = ref.astype(np.float32).astype(np.float64)
+        assert (np.abs(want[np.isfinite(want)]) > 3.3e38).any()
+        got = out.cpu().numpy().astype(np.float64)
+        assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+        fin = np.isfinite(want)
+        assert (np.abs(got[fin] - want[fin]) <= REL_TOL * ab[fin] + ABS_TOL).all()
