@@ -24,8 +24,8 @@
 //  * the A fragment of (group, tap) is four 8-byte loads from the filter
 //    packed by spconv_pack_dense, two steps ahead, split in registers;
 //  * the epilogue adds bias (and a residual), applies ReLU, pools 2x2 windows
-//    through LDS when asked, and stores once. Outputs that are not finite are
-//    summed again in plain fp32: infinities (and values that round to one in bf16)
+//    through LDS when asked, and stores once. Sums that are not finite are taken
+//    again on the fp32 MFMA: infinities (and values that round to one in bf16)
 //    have no finite parts, and near the top of the range h rounds up past the
 //    value, so that hh can overflow where the product does not.
 #include <hip/hip_runtime.h>
@@ -139,20 +139,6 @@ __device__ __forceinline__ void dense_put(const DenseArgs &a, char *buf, const S
     *reinterpret_cast<u32x4_t *>(d + a.PX * 64) = p.l;
 }
 
-// Plain fp32 sum of one output, for results that are not finite.
-template <int R, int S>
-__device__ __forceinline__ float dense_sum_fp32(const float *__restrict__ img, const float *__restrict__ wk,
-                                                          int C, int Kp, int IH, int IW, int y, int x) {
-    float s = 0.0f;
-    for (int c = 0; c < C; ++c)
-        for (int t = 0; t < R * S; ++t) {
-            const int yy = y + t / S, xx = x + t % S;
-            const float v = (yy >= 0 && yy < IH && xx >= 0 && xx < IW) ? img[((size_t)c * IH + yy) * IW + xx] : 0.0f;
-            s = fmaf(wk[((size_t)(c >> 1) * R * S + t) * Kp * 2 + (c & 1)], v, s);
-        }
-    return s;
-}
-
 // What bounds it: at 14x14 (256 channels, batch 32, one workgroup per CU) the
 // MFMAs alone take about 33 us (the chip holds 1.65 PFLOP/s on this MFMA form)
 // and everything else (the A loads and their split, LDS reads, staging) about
@@ -183,10 +169,10 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
     const int lane = (int)threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int work = xcd_linear_id((int)blockIdx.x, a.total_wgs);
-    const int kt = work % a.nkt;
+    const int kt = __builtin_amdgcn_readfirstlane(work % a.nkt);
     const int rest = work / a.nkt;
-    const int ty = rest % a.ntiles_y;
-    const int n = rest / a.ntiles_y;
+    const int ty = __builtin_amdgcn_readfirstlane(rest % a.ntiles_y);
+    const int n = __builtin_amdgcn_readfirstlane(rest / a.ntiles_y);
     const int y0 = ty * a.TH;
     // channel tile, reduction share, pixel share
     const int wn = __builtin_amdgcn_readfirstlane(wave % a.nw);
@@ -381,13 +367,75 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[b][r] += low[b][r];
 
+    // (The lane counted again: the values above would stay in registers through the loop.)
+    const int elane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    const int ehalf = elane >> 5, ecol = elane & 31;
+    // Row and column of the lane's pixel in each block, virtual pixel q0 + 32*b of
+    // the tile and on (row -1: not stored).
+    int ys[NBW], xs[NBW];
+#pragma unroll
+    for (int b = 0; b < NBW; ++b) {
+        const int q = q0 + kDnsTile * b + ecol;
+        const int yl = (int)fast_div((uint32_t)q, a.wp_magic, a.wp_shift), x = q - yl * a.Wp;
+        const bool in = yl < a.TH && x < a.Wo && y0 + yl < a.Ho;
+        ys[b] = in ? y0 + yl : -1;
+        xs[b] = x;
+    }
+    // A wave with a sum that is not finite takes its share of the sums again on the
+    // fp32 MFMA (see the file comment), a filter row of a channel pair at a time
+    // from global memory, and keeps the new value where the old one is not finite.
+    // With NaN in every pixel 14x14, 256 channels, batch 32 takes 211 us (59 without;
+    // 1623 where each lane summed its outputs one after another).
+    bool bad = false;
+#pragma unroll
+    for (int b = 0; b < NBW; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) bad |= ys[b] >= 0 && !(fabsf(acc[b][r]) < INFINITY);
+    if (__builtin_amdgcn_ballot_w64(bad)) {
+#pragma unroll
+        for (int b = 0; b < NBW; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) low[b][r] = 0.0f;
+        for (int g = wr; g < ngroups; g += a.ksr)
+            for (int cp = 8 * g; cp < min(8 * g + 8, npairs); ++cp) {
+                const int c = 2 * cp + ehalf;  // (past the last channel of an odd count: zeros)
+                const float *plane = xp + ((size_t)n * a.C + min(c, a.C - 1)) * a.IH * a.IW;
+#pragma unroll 1
+                for (int r = 0; r < R; ++r) {
+                    float w[S], v[S][NBW];
+                    int at[S][NBW];
+#pragma unroll
+                    for (int t = 0; t < S; ++t) {
+                        w[t] = wpk[((size_t)(cp * RS + r * S + t) * a.Kp + k0 + ecol) * 2 + ehalf];
+#pragma unroll
+                        for (int b = 0; b < NBW; ++b) {
+                            const int y = ys[b] + r - a.ipad, x = xs[b] + t - a.ipad;
+                            const bool in = ys[b] >= 0 && c < a.C && y >= 0 && y < a.IH && x >= 0 && x < a.IW;
+                            at[t][b] = in ? y * a.IW + x : -1;
+                            v[t][b] = plane[max(at[t][b], 0)];  // (no branch around the load)
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);  // (the compiler would wait for each load in turn)
+#pragma unroll
+                    for (int t = 0; t < S; ++t)
+#pragma unroll
+                        for (int b = 0; b < NBW; ++b)
+                            low[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[t], at[t][b] >= 0 ? v[t][b] : 0.0f, low[b], 0, 0, 0);
+                }
+            }
+#pragma unroll
+        for (int b = 0; b < NBW; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[b][r] = fabsf(acc[b][r]) < INFINITY ? acc[b][r] : low[b][r];
+    }
+
     // Sum the ksr partial tiles, in order 0, 1, ..., through LDS; wave wr keeps
     // accumulator registers wr*J .. wr*J + J - 1 (fin[b][jj], J = 16 / ksr), so
     // every wave has a share of the epilogue.
     const int J = 16 / a.ksr, j0 = wr * J;
     if (a.ksr > 1) {
         __syncthreads();  // the chunk buffers are free
-        float *red = lds + (size_t)(wp * a.nw + wn) * a.ksr * NBW * 16 * kWave + lane;
+        float *red = lds + (size_t)(wp * a.nw + wn) * a.ksr * NBW * 16 * kWave + elane;
 #pragma unroll
         for (int b = 0; b < NBW; ++b)
 #pragma unroll
@@ -405,49 +453,11 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
         }
     }
 
-    // acc[b][jj] is channel chan(jj) at virtual pixel q0 + 32*b + col of the
-    // tile. Row and column of the lane's pixel in each block (-1: not stored).
+    // acc[b][jj] is channel chan(jj) of pixel (ys[b], xs[b]).
     auto chan = [&](int jj) {
         const int j = j0 + jj;
-        return k0 + 8 * (j >> 2) + 4 * half + (j & 3);
+        return k0 + 8 * (j >> 2) + 4 * ehalf + (j & 3);
     };
-    int ys[NBW], xs[NBW];
-#pragma unroll
-    for (int b = 0; b < NBW; ++b) {
-        const int q = q0 + kDnsTile * b + col;
-        const int yl = (int)fast_div((uint32_t)q, a.wp_magic, a.wp_shift), x = q - yl * a.Wp;
-        const bool in = yl < a.TH && x < a.Wo && y0 + yl < a.Ho;
-        ys[b] = in ? y0 + yl : -1;
-        xs[b] = x;
-    }
-    // Stored sums that are not finite are taken again in fp32 (see the file comment).
-    uint64_t redo = 0;
-#pragma unroll
-    for (int b = 0; b < NBW; ++b)
-#pragma unroll
-        for (int jj = 0; jj < 16; ++jj)
-            if (jj < J && ys[b] >= 0 && chan(jj) < a.K && !(fabsf(acc[b][jj]) < INFINITY)) redo |= 1ull << (b * 16 + jj);
-    if (__builtin_amdgcn_ballot_w64(redo != 0)) {
-        const float *img = xp + (size_t)n * a.C * a.IH * a.IW;
-        while (redo) {
-            const int e = __builtin_ctzll(redo);
-            redo &= redo - 1;
-            int y = 0, x = 0;
-#pragma unroll
-            for (int b = 0; b < NBW; ++b)
-                if (b == e >> 4) {
-                    y = ys[b];
-                    x = xs[b];
-                }
-            const float s = dense_sum_fp32<R, S>(img, wpk + (size_t)chan(e & 15) * 2, a.C, a.Kp, a.IH, a.IW,
-                                                 y - a.ipad, x - a.ipad);
-#pragma unroll
-            for (int b = 0; b < NBW; ++b)
-#pragma unroll
-                for (int jj = 0; jj < 16; ++jj)
-                    if (e == b * 16 + jj) acc[b][jj] = s;
-        }
-    }
 
     // Bias, residual and ReLU of registers 4*gq .. 4*gq + 3 (the residuals of
     // all blocks are loaded before the first is used).
@@ -495,7 +505,7 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
             const int r1 = min(y0 + a.TH, a.Ho);
             for (int kk = k0 + share; kk < min(k0 + kDnsTile, a.K); kk += shares)
                 zero_border(out + ((size_t)n * a.K + kk) * a.oplane, y0, r1, a.Ho, a.Wo, a.out_pad, a.opitch, ty == 0,
-                            ty == a.ntiles_y - 1, lane, kWave);
+                            ty == a.ntiles_y - 1, elane, kWave);
         }
     } else {
         // Pool through LDS, 8 channels of each (channel tile, reduction share)
@@ -515,9 +525,9 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
             for (int u = 0; u < 4; ++u)
 #pragma unroll
                 for (int b = 0; b < NBW; ++b)
-                    st[(4 * half + u) * px + q0 + kDnsTile * b + col] = acc[b][4 * gq + u];
+                    st[(4 * ehalf + u) * px + q0 + kDnsTile * b + ecol] = acc[b][4 * gq + u];
             __syncthreads();
-            for (int t = wp * kWave + lane; t < kDnsPoolCh * per_ch; t += a.ksp * kWave) {
+            for (int t = wp * kWave + elane; t < kDnsPoolCh * per_ch; t += a.ksp * kWave) {
                 const int cc = (int)fast_div((uint32_t)t, a.pch_magic, a.pch_shift);
                 const int rem = t - cc * per_ch;
                 const int r = (int)fast_div((uint32_t)rem, a.wq_magic, a.wq_shift), jq = rem - r * a.Wq;
@@ -536,7 +546,7 @@ __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs 
             const int r1 = min(prow0 + prows, a.Hq);
             for (int kk = k0 + share; kk < min(k0 + kDnsTile, a.K); kk += shares)
                 zero_border(out + ((size_t)n * a.K + kk) * a.oplane, prow0, r1, a.Hq, a.Wq, a.out_pad, a.opitch,
-                            ty == 0, ty == a.ntiles_y - 1, lane, kWave);
+                            ty == 0, ty == a.ntiles_y - 1, elane, kWave);
         }
     }
 }

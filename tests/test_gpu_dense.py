@@ -272,3 +272,28 @@ def test_dense_results_near_the_top_of_the_range(sp, C, K, H, W, pool):
     assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
     fin = np.isfinite(want)
     assert (np.abs(got[fin] - want[fin]) <= REL_TOL * ab[fin] + ABS_TOL).all()
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_dense_input_without_a_finite_value(sp, value):
+    """Every sum not finite (a diverged network): what fp32 gives on the CPU, for
+    one, two and four reduction shares and tap pairs. (Taking these sums again
+    one output at a time took hundreds of times a normal pass.)"""
+    import torch
+    for N, C, K, H, W, pool in [(2, 48, 64, 14, 14, False), (1, 40, 33, 9, 30, True), (2, 3, 40, 7, 9, False),
+                                (64, 32, 128, 14, 14, False)]:
+        layer = synth.random_layer(8600 + C, N, C, K, H, W, 3, 3, 1, 1, 1.0, False, pool, True, False)
+        L = sp.SparseConvLayer(layer.w, None, layer.bias, H, W, 1, 1, False, pool, path="dense")
+        say("dense", value, L.plan(N))
+        x = torch.full((N, C, H, W), value)
+        out = L.run(x.cuda()).cpu()
+        ref = torch.nn.functional.conv2d(x[:1], torch.from_numpy(layer.w), torch.from_numpy(layer.bias), padding=1)
+        assert not torch.isfinite(ref).any()
+        if pool:  # a window's maximum skips NaN, unless all four are
+            ref = torch.nan_to_num(ref, nan=-float("inf"), posinf=float("inf"), neginf=-float("inf"))
+            assert not torch.isfinite(out).any()
+            m = torch.nn.functional.max_pool2d(ref, 2)
+            assert torch.equal(out == float("inf"), (m == float("inf")).expand_as(out))
+            continue
+        assert torch.equal(torch.isnan(out), torch.isnan(ref).expand_as(out))
+        assert torch.equal(torch.nan_to_num(out), torch.nan_to_num(ref).expand_as(out))

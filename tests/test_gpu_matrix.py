@@ -224,3 +224,30 @@ def test_results_near_the_top_of_the_range(sp):
         assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
         fin = np.isfinite(want)
         assert (np.abs(got[fin] - want[fin]) <= REL_TOL * ab[fin] + ABS_TOL).all()
+
+
+@pytest.mark.parametrize("value", [float("inf"), -float("inf"), float("nan")])
+@pytest.mark.parametrize("i", [1, 4, 6, 12, 15, 16])
+def test_input_without_a_finite_value(sp, i, value):
+    """Every sum not finite (a diverged network), whole rows of entries taken again
+    in fp32: what the entries' signs give. (Taking these sums again one output
+    at a time took a hundred times a normal pass.)"""
+    import torch
+    layer = _layer(i)
+    L, _ = _on_device(sp, layer)
+    L.flags = 0
+    N, C, H, W, K, R, S = layer.shape
+    x = np.full(layer.x.shape, value, np.float32)
+    out = L.forward_padded(L.pad_input(torch.from_numpy(x).cuda())).cpu().numpy()
+    xp = np.pad(x[:1], ((0, 0), (0, 0), (layer.pad,) * 2, (layer.pad,) * 2))
+    st, (Ho, Wo) = layer.stride, out.shape[2:]
+    bias = np.zeros(K, np.float32) if layer.bias is None else layer.bias
+    ref = np.repeat(np.repeat(bias[None, :, None, None], Ho, 2), Wo, 3)
+    with np.errstate(all="ignore"):
+        for k in range(K):
+            for c, r, s in np.argwhere(layer.mask[k]):
+                ref[:, k] += layer.w[k, c, r, s] * xp[:, c, r:r + st * Ho - st + 1:st, s:s + st * Wo - st + 1:st]
+    fin = np.isfinite(ref)
+    for n in range(N):
+        assert np.array_equal(out[n][~fin[0]], ref[0][~fin[0]], equal_nan=True)
+        assert np.allclose(out[n][fin[0]], ref[0][fin[0]], rtol=1e-5, atol=1e-6)
