@@ -561,10 +561,14 @@ class SparseConvLayer:
         """Whether ``forward`` forms the zero border in the kernel (it can, and
         that beats a pad pass: always for the dense and matrix kernels, which
         read their input through registers, for the sparse stride-1 kernel on
-        rows of whole 16-byte groups)."""
-        if not self.can_pad_in_kernel(N):
-            return False
-        return self.path == "dense" or self.W % 4 == 0 or self.plan(N)["kernel"] == SPCONV_KERNEL_MATRIX
+        rows of whole 16-byte groups). Asked on every ``forward``: decided once
+        per batch size and flags (two plans take 13 us of host time)."""
+        cache = self.__dict__.setdefault("_pads_in_kernel", {})
+        key = (N, self.flags)
+        if key not in cache:
+            cache[key] = self.can_pad_in_kernel(N) and (
+                self.path == "dense" or self.W % 4 == 0 or self.plan(N)["kernel"] == SPCONV_KERNEL_MATRIX)
+        return cache[key]
 
     def forward(self, x, out=None, stream=None, out_pad: int = 0, residual=None, residual_pad: int = 0, xp=None,
                 pad_in_kernel: bool | None = None):
