@@ -133,7 +133,9 @@ def spconv_strerror(code: int) -> str:
     return _lib.spconv_strerror(int(code)).decode()
 
 
-@lru_cache(maxsize=1024)  # a function of its integers alone, asked several times per forward call
+# A function of its integers alone, asked several times per forward call (typed: a
+# float that equals a remembered integer is refused as ever).
+@lru_cache(maxsize=1024, typed=True)
 def spconv_output_shape(H, W, R, S, stride, pad, flags):
     ho, wo = _c_int(), _c_int()
     _check(_lib.spconv_output_shape(H, W, R, S, stride, pad, flags, ctypes.byref(ho), ctypes.byref(wo)),

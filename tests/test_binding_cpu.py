@@ -39,3 +39,10 @@ def test_pads_in_kernel_plans_once(sp, monkeypatch, W, density, path, stride, wa
     layer.pads_in_kernel(8)
     del asked[:]
     assert layer.pads_in_kernel(8) is layer.pads_in_kernel(8) and not asked
+
+
+def test_output_shape_refuses_floats_it_has_answered_as_integers(sp):
+    assert sp.spconv_output_shape(14, 14, 3, 3, 1, 1, 1) == (14, 14)
+    for args in [(14.0, 14, 3, 3, 1, 1, 1), (14, 14, 3, 3, 1.0, 1, 1), (14, 14, 3, 3, 1, 1, 1.0)]:
+        with pytest.raises(ctypes.ArgumentError):
+            sp.spconv_output_shape(*args)
