@@ -415,7 +415,8 @@ int spconv_pack_dense(const float *w, const uint8_t *mask, int K, int C, int R, 
  * filter other than 3x3 or 1x1, unknown flags, pool with Ho or Wo < 2,
  * C*Hp*Wp >= 2^31, a packed filter of 2^31 bytes or more, bad border
  * options as in spconv_forward_ex, or no tiling
- * that fits the kernel: the padded row wider than 255 floats, 127 with pool);
+ * that fits the kernel: the padded row wider than 255 floats, 127 with pool, or
+ * min(C, 16) padded planes of more than 2^32 - 16 bytes);
  * SPCONV_EHIP when the launch fails.
  */
 int spconv_forward_dense(const float *in_padded, int N, int C, int H, int W, const float *packed, int K, int R, int S,

@@ -102,7 +102,7 @@ __device__ __forceinline__ StageTask dense_task(const DenseArgs &a, int id, int 
         const int i = (int)fast_div((uint32_t)px, a.wp_magic, a.wp_shift);
         const int y = y0 + i - a.ipad, x = px - i * a.Wp - a.ipad;
         t.lds = (oct >> 1) * a.PX * kDnsPxBytes + ((oct & 1) * a.PX + px) * 16;
-        if (y >= 0 && y < a.IH && x >= 0 && x < a.IW)
+        if (oct * 8 < a.C && y >= 0 && y < a.IH && x >= 0 && x < a.IW)
             t.voff = (uint32_t)((oct * 8 * a.IH + y) * a.IW + x) * (uint32_t)sizeof(float);
     }
     return t;
@@ -121,11 +121,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t dense_chunk_rsrc(const DenseAr
 __device__ __forceinline__ void dense_load(const DenseArgs &a, const __amdgpu_buffer_rsrc_t &rsrc, const StageTask &t,
                                            float (&v)[8]) {
     const uint32_t pb = (uint32_t)(a.IH * a.IW) * (uint32_t)sizeof(float);
-    // A border pixel's offset stays past the range (no wrap): the step is 0 there.
-    const uint32_t step = t.voff == 0xfffffff0u ? 0u : pb;
+    // Saturating steps: offsets past the range (border pixels, channels past C)
+    // stay there and do not wrap.
+    uint32_t off = t.voff;
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-        v[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, t.voff + j * step, 0, 0));
+    for (int j = 0; j < 8; ++j) {
+        v[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, off, 0, 0));
+        off = __builtin_elementwise_add_sat(off, pb);
+    }
 }
 
 __device__ __forceinline__ void dense_put(const DenseArgs &a, char *buf, const StageTask &t, const float (&v)[8]) {
@@ -632,7 +635,9 @@ int dense_split(long long base_waves, int nw) {
 // from there on; where the partial tiles or a chunk of that many groups do not
 // fit the LDS they share pixels only. A chunk holds as many channel groups as
 // threads can load ahead (kDnsRounds tasks each), in two buffers where they fit.
-bool dense_layout_tile(int C, int Wp, int Wo, int R, int S, bool pool, int ws, DensePlan *q) {
+// A chunk's channels lie within 32-bit byte offsets (`plane_bytes` each).
+bool dense_layout_tile(int C, long long plane_bytes, int Wp, int Wo, int R, int S, bool pool, int ws, DensePlan *q) {
+    const long long range = 0xfffffff0LL / plane_bytes;  // channels in reach
     const int valid = (q->TH - 1) * Wp + Wo;  // virtual pixels up to the last stored one
     const int nbv = (valid + kDnsTile - 1) / kDnsTile;
     const int ngroups = (C + kDnsGroup - 1) / kDnsGroup;
@@ -650,6 +655,8 @@ bool dense_layout_tile(int C, int Wp, int Wo, int R, int S, bool pool, int ws, D
         const int threads = q->nw * ws * kWave;
         int gmax = (int)std::min<long long>((kDnsLdsBytes - slack) / unit, 1 << 20);
         if (gmax < 1 && unit + slack <= kDnsLdsMax) gmax = 1;
+        if (std::min(C, kDnsGroup) > range) return false;
+        if (C > range) gmax = std::min(gmax, (int)(range / kDnsGroup));
         if (gmax < ksr) continue;
         const int ahead = std::max(1, kDnsRounds * threads / (2 * q->PX));  // groups loaded ahead
         int Cg = std::min({ahead, gmax, ngroups});
@@ -689,9 +696,9 @@ bool plan_dense(int N, int C, int K, int H, int W, int pad, int Wp, int Ho, int 
         if (q.NB > kDnsMaxBlocks) break;
         q.ntiles_y = (Ho + th - 1) / th;
         const long long base_waves = (long long)N * q.ntiles_y * q.nkt * q.nw;
-        if (!dense_layout_tile(C, Wp, Wo, R, S, pool, dense_split(base_waves, q.nw), &q)) continue;
-        // The load offsets of one chunk are 32-bit byte offsets.
-        if ((long long)q.Cg * kDnsGroup * (H + 2LL * pad) * Wp * 4 >= (1LL << 31)) continue;
+        if (!dense_layout_tile(C, (H + 2LL * pad) * Wp * (long long)sizeof(float), Wp, Wo, R, S, pool,
+                               dense_split(base_waves, q.nw), &q))
+            continue;
         const long long waves = base_waves * q.ksr * q.ksp;
         const long long cost = (long long)q.ntiles_y * (q.NB + 1);
         bool better;

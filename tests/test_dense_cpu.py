@@ -133,3 +133,22 @@ def test_select_path(sp):
     assert lib.spconv_select_path(32, 64, 56, 56, 64, 3, 3, 1, 1, -1, 1, ctypes.byref(out)) == E
     assert lib.spconv_select_path(32, 64, 56, 56, 64, 3, 3, 1, 1, 64 * 64 * 9 + 1, 1, ctypes.byref(out)) == E
     assert lib.spconv_select_path(32, 64, 56, 56, 64, 3, 3, 0, 1, 7280, 1, ctypes.byref(out)) == E
+
+
+@pytest.mark.parametrize("N,C,K,H,W,R,pad", [(1, 33, 64, 89173, 166, 1, 0), (62, 12, 30, 161659, 229, 3, 0),
+                                             (1, 1, 8, 2_100_000, 254, 3, 0), (1, 2, 8, 2_100_000, 253, 3, 1),
+                                             (1, 3, 8, 699_000, 253, 3, 1), (1, 16, 8, 230_000, 253, 3, 1),
+                                             (1, 40, 8, 200_000, 253, 3, 1), (1, 2, 40, 16_000_000, 32, 1, 0)])
+def test_tall_planes_have_a_plan(sp, N, C, K, H, W, R, pad):
+    """A chunk's bytes are those of the channels there are (not of whole groups of
+    16), and of as few groups as the byte offsets reach."""
+    p = sp.spconv_dense_plan(N, C, H, W, K, R, R, pad, 1)
+    plane = (H + 2 * pad) * (W + 2 * pad) * 4
+    assert min(C, p["channels_per_chunk"]) * plane <= 0xfffffff0
+
+
+def test_planes_past_the_offsets_are_refused(sp):
+    for C, H in [(16, 263_200), (17, 263_200), (100, 263_200)]:  # 16 planes of 2^32 bytes
+        if C * H * 255 < 1 << 31:
+            with pytest.raises(sp.SpconvError):
+                sp.spconv_dense_plan(1, C, H, 255, 8, 1, 1, 0, 1)

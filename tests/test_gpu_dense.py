@@ -297,3 +297,31 @@ def test_dense_input_without_a_finite_value(sp, value):
             continue
         assert torch.equal(torch.isnan(out), torch.isnan(ref).expand_as(out))
         assert torch.equal(torch.nan_to_num(out), torch.nan_to_num(ref).expand_as(out))
+
+
+@pytest.mark.parametrize("C,H,W,R", [(2, 2_100_000, 253, 3), (13, 620_000, 131, 1), (16, 230_000, 253, 3),
+                                     (40, 200_000, 253, 3)])
+def test_dense_tall_planes(sp, C, H, W, R):
+    """Chunks near the end of 32-bit byte offsets (8 GB of input): bands of rows at the
+    ends and between against float64, the rest finite and where the ReLU left it."""
+    import torch
+    K, pad = 2, R // 2
+    layer = synth.random_layer(8700 + C, 1, C, K, 8, 8, R, R, 1, pad, 1.0, True, False, True, False)
+    L = sp.SparseConvLayer(layer.w, None, layer.bias, H, W, 1, pad, True, False, path="dense")
+    say("dense tall planes", C, H, W, L.plan(1))
+    g = torch.Generator(device="cuda").manual_seed(C)
+    x = torch.rand((1, C, H, W), generator=g, device="cuda")
+    out = L.forward(x)
+    torch.cuda.synchronize()
+    w, b = torch.from_numpy(layer.w).double(), torch.from_numpy(layer.bias).double()
+    for r0 in (0, H // 3, H // 2 + 7, H - 20):
+        r1 = min(H, r0 + 20)
+        lo, hi = max(0, r0 - pad), min(H, r1 + pad)
+        band = torch.nn.functional.pad(x[:, :, lo:hi].cpu().double(),
+                                       (pad, pad, pad - (r0 - lo), pad - (hi - r1)))
+        ref = torch.relu(torch.nn.functional.conv2d(band, w, b))
+        ab = torch.nn.functional.conv2d(band, w.abs(), b.abs())
+        check_close(out[:, :, r0:r1].cpu().numpy(), ref.numpy(), ab.numpy(), f"rows {r0}..")
+    assert bool((out >= 0).all()) and bool(torch.isfinite(out).all())
+    del x, out
+    torch.cuda.empty_cache()
