@@ -18,8 +18,10 @@
  *
  * Every call returns an int status (SPCONV_OK or a negative code) and never
  * throws. Argument checks happen on the host before any GPU work is queued.
- * The caller owns every buffer; the library keeps no state, so calls on
- * different streams may run concurrently.
+ * The caller owns every buffer. The library keeps no state that a result depends
+ * on (it remembers the plans of recent calls, a bounded table behind a lock, and
+ * which kernels have had their LDS limit raised), so calls on different streams
+ * and from different threads may run concurrently.
  */
 #ifndef SPCONV_H
 #define SPCONV_H

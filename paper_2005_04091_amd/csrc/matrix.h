@@ -31,6 +31,14 @@ struct MatrixCall {
 bool matrix_plan(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, bool pool, long long nnz,
                  MatrixPlan *out);
 
+// What was decided for recent calls of these shapes (thread safe, bounded):
+// recall fills *plan and *use (whether they run on this kernel) and returns true
+// when it remembers one.
+bool matrix_recall(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, bool pool, long long nnz,
+                   MatrixPlan *plan, bool *use);
+void matrix_remember(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, bool pool, long long nnz,
+                     const MatrixPlan &plan, bool use);
+
 // (16-pixel blocks per wave, 0, channels per wave, pool) of the compiled instances.
 void matrix_variants(int32_t *variants, int32_t capacity, int32_t *count);
 

@@ -764,48 +764,80 @@ bool search_plan(int N, int C, int H, int W, int K, int R, int S, int stride, in
     return true;
 }
 
-// Plans of recent calls. The search tries some thousand tilings (tens of
-// microseconds of host time), and a program calls the same few layers again
-// and again: a small table, one slot per hash, holds the last ones. A plan is
-// a function of the shapes alone.
-struct PlanKey {
+// Choices of recent calls: whether a call runs here, and on which plan. They are
+// functions of its shapes and entry count alone, and finding one takes the host
+// some thousand tilings (11 to 34 us, as much as a launch), while a program calls
+// the same layers again and again. 128 sets of eight, the least recently used one
+// of a set replaced: a network's layers at a few batch sizes stay (a table of 64
+// single slots lost half of ten layers to each other).
+struct ChoiceKey {
     int v[10];
     long long nnz;
-    bool operator==(const PlanKey &o) const { return std::equal(v, v + 10, o.v) && nnz == o.nnz; }
+    bool operator==(const ChoiceKey &o) const { return std::equal(v, v + 10, o.v) && nnz == o.nnz; }
 };
+
+struct Choice {
+    ChoiceKey key{};
+    MatrixPlan plan;
+    bool use = false;
+    uint64_t used = 0;  // turn of the last use, 0: empty
+};
+
+constexpr int kChoiceSets = 128, kChoiceWays = 8;
+std::mutex choice_mutex;
+Choice choices[kChoiceSets][kChoiceWays];
+uint64_t choice_turn = 0;
+
+ChoiceKey choice_key(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, bool pool, long long nnz) {
+    return {{N, C, H, W, K, R, S, stride, pad, pool ? 1 : 0}, nnz};
+}
+
+Choice *choice_set(const ChoiceKey &key) {
+    uint64_t h = (uint64_t)key.nnz;
+    for (int v : key.v) h = (h ^ (uint64_t)(uint32_t)v) * 0x9e3779b97f4a7c15ull;
+    return choices[(h >> 40) % kChoiceSets];
+}
 
 }  // namespace
 
 __attribute__((visibility("hidden"))) bool matrix_plan(int N, int C, int H, int W, int K, int R, int S, int stride,
                                                        int pad, bool pool, long long nnz, MatrixPlan *out) {
-    constexpr int kSlots = 64;
-    struct Slot {
-        PlanKey key{};
-        MatrixPlan plan;
-        bool used = false, ok = false;
-    };
-    static std::mutex mu;
-    static Slot slots[kSlots];
-    const PlanKey key = {{N, C, H, W, K, R, S, stride, pad, pool ? 1 : 0}, nnz};
-    uint64_t h = (uint64_t)nnz;
-    for (int v : key.v) h = (h ^ (uint64_t)(uint32_t)v) * 0x9e3779b97f4a7c15ull;
-    Slot &slot = slots[(h >> 40) % kSlots];
-    {
-        std::lock_guard<std::mutex> lock(mu);
-        if (slot.used && slot.key == key) {
-            *out = slot.plan;
-            return slot.ok;
+    return search_plan(N, C, H, W, K, R, S, stride, pad, pool, nnz, out);
+}
+
+__attribute__((visibility("hidden"))) bool matrix_recall(int N, int C, int H, int W, int K, int R, int S, int stride,
+                                                         int pad, bool pool, long long nnz, MatrixPlan *plan, bool *use) {
+    const ChoiceKey key = choice_key(N, C, H, W, K, R, S, stride, pad, pool, nnz);
+    Choice *set = choice_set(key);
+    std::lock_guard<std::mutex> lock(choice_mutex);
+    for (int i = 0; i < kChoiceWays; ++i)
+        if (set[i].used && set[i].key == key) {
+            set[i].used = ++choice_turn;
+            *plan = set[i].plan;
+            *use = set[i].use;
+            return true;
         }
+    return false;
+}
+
+__attribute__((visibility("hidden"))) void matrix_remember(int N, int C, int H, int W, int K, int R, int S, int stride,
+                                                           int pad, bool pool, long long nnz, const MatrixPlan &plan,
+                                                           bool use) {
+    const ChoiceKey key = choice_key(N, C, H, W, K, R, S, stride, pad, pool, nnz);
+    Choice *set = choice_set(key);
+    std::lock_guard<std::mutex> lock(choice_mutex);
+    Choice *slot = set;
+    for (int i = 0; i < kChoiceWays; ++i) {
+        if (set[i].used && set[i].key == key) {  // (another thread was first)
+            slot = set + i;
+            break;
+        }
+        if (set[i].used < slot->used) slot = set + i;
     }
-    MatrixPlan plan;
-    const bool ok = search_plan(N, C, H, W, K, R, S, stride, pad, pool, nnz, &plan);
-    *out = plan;
-    std::lock_guard<std::mutex> lock(mu);
-    slot.key = key;
-    slot.plan = plan;
-    slot.ok = ok;
-    slot.used = true;
-    return ok;
+    slot->key = key;
+    slot->plan = plan;
+    slot->use = use;
+    slot->used = ++choice_turn;
 }
 
 __attribute__((visibility("hidden"))) void matrix_variants(int32_t *variants, int32_t capacity, int32_t *count) {

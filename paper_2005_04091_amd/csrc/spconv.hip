@@ -2198,8 +2198,7 @@ namespace {
 // the row hint (whose imbalance factor orders tilings and overstates times), so
 // that the choice, and with it the order of the sums, depends on neither.
 bool use_matrix(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, bool pool, long long nnz,
-                const Plan &pl, MatrixPlan *mp) {
-    if (C < 8) return false;
+                const Plan &pl, MatrixPlan *mp) {  // C >= 8
     if (stride != 1) return matrix_plan(N, C, H, W, K, R, S, stride, pad, pool, nnz, mp);
     const double walk_us = 7.5 + 0.27e-3 * pl.time;
     if ((long long)H * W < 49 || walk_us < 15.0 || !matrix_plan(N, C, H, W, K, R, S, stride, pad, pool, nnz, mp)) return false;
@@ -2251,11 +2250,16 @@ int prepare_forward(int N, int C, int H, int W, const spconv_csr *csr, int K, in
     }
     if (!ok) return SPCONV_EINVAL;
     if (unpadded && pl.kind != Kind::kStride1) return SPCONV_EINVAL;
-    if (mp && !lowered) {
-        Plan plain = pl;  // for the padded input, without the hint
-        if (stride == 1 && (row16 || max_row_nnz > 0))
-            ok = plan_stride1(N, C, K, (int)Hp, (int)Wp, (int)Wp, 0, Ho, Wo, R, S, pool, csr->nnz, 0, false, &plain);
-        if (!ok || !use_matrix(N, C, H, W, K, R, S, stride, pad, pool, csr->nnz, plain, mp)) mp->total_wgs = 0;
+    if (mp && !lowered && C >= 8) {
+        bool use = false;
+        if (!matrix_recall(N, C, H, W, K, R, S, stride, pad, pool, csr->nnz, mp, &use)) {
+            Plan plain = pl;  // for the padded input, without the hint
+            if (stride == 1 && (row16 || max_row_nnz > 0))
+                ok = plan_stride1(N, C, K, (int)Hp, (int)Wp, (int)Wp, 0, Ho, Wo, R, S, pool, csr->nnz, 0, false, &plain);
+            use = ok && use_matrix(N, C, H, W, K, R, S, stride, pad, pool, csr->nnz, plain, mp);
+            matrix_remember(N, C, H, W, K, R, S, stride, pad, pool, csr->nnz, *mp, use);
+        }
+        if (!use) mp->total_wgs = 0;
     }
     FwdArgs a;
     a.unpadded = unpadded ? 1 : 0;
