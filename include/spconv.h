@@ -300,7 +300,16 @@ int spconv_pack_lowered(int N, int C, int H, int W, const spconv_csr *csr, int K
 #define SPCONV_KERNEL_STRIDE1_TILED 4
 /* CSR filter on the matrix cores, for calls without a lowered stream: strided
  * layers of 8 or more input channels, and stride-1 ones where it is modelled
- * faster than the stride-1 kernel (dense enough filters). */
+ * faster than the stride-1 kernel (dense enough filters).
+ * Arithmetic of this kernel and of the dense one: fp32 values as three bf16 parts
+ * each, six part products to a product, fp32 sums. For inputs and filter values
+ * of 2^-110 (8e-34) or more in magnitude (or zero) a product is within 2^-23 of
+ * exact, and a sum's error is that of a chain of fp32 products or less. Smaller
+ * values are taken to the nearest multiple of 2^-133, so they count with fewer
+ * bits (within 5e-5 of 1e-36). Sums that are not
+ * finite are taken again in fp32 (infinities and NaN as the other kernels give
+ * them), which makes calls with many of them slower (all of them: up to 4 times
+ * as long on the dense kernel, 3 to 17 times on this one). */
 #define SPCONV_KERNEL_MATRIX 5
 
 typedef struct spconv_plan_info {
@@ -373,8 +382,9 @@ int spconv_kernel_variants(int32_t kernel, int32_t *variants, int32_t capacity, 
 /*
  * Dense path. Above some density, skipping zeros no longer pays: the same
  * fused convolution computed with every filter tap on the matrix cores
- * (fp32 values as three bf16 parts each, fp32 sums: the error is that of the
- * sparse path's fp32 arithmetic or less) is faster.
+ * is faster (arithmetic: see SPCONV_KERNEL_MATRIX; every tap is multiplied, so
+ * that an infinity or NaN of the input also reaches the outputs that read it
+ * under a zero of the filter).
  * The paper reports that its sparse kernels beat the dense ones only below a
  * break-even density (Evaluation, sparse versus dense, on its CPUs); these
  * calls give the same choice on MI355X: spconv_select_path predicts which

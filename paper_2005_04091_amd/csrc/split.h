@@ -1,10 +1,19 @@
 // fp32 values as three bf16 parts, for the kernels that form fp32 products on
-// the bf16 matrix cores (internal header). x = h + m + l exactly: each part is
-// the bf16 rounding of what the parts before it leave, which has at most 16,
-// then 8 significant bits. A product of two such values takes the six part
-// products of weight 2^-16 or more (hh, hm, mh, mm, hl, lh); what is dropped
-// is at most 2^-23 of it and 2^-26 on average. Infinities (and values that round to one in bf16) have
-// no finite parts: every sum they enter is NaN.
+// the bf16 matrix cores (internal header). Each part is the bf16 rounding of what
+// the parts before it leave, which has at most 16, then 8 significant bits.
+//  * x = h + m + l exactly for 2^-110 <= |x| < 2^128 - 2^119. Below, the last bits
+//    lie under bf16's least subnormal, 2^-133: the parts are then x to the nearest
+//    multiple of that (an error of up to 2^-134: 2^-24 of x at 2^-110, 5e-5 of
+//    1e-36). From 2^128 - 2^119 on, and for infinities and NaN, h is not finite
+//    and neither is any sum x enters.
+//  * A product of two such values takes the six part products of weight 2^-16 or
+//    more (hh, hm, mh, mm, hl, lh); the three dropped are at most 2^-24 of it
+//    together (2^-26 on average). With the rounding of the sum a single product
+//    is within 2^-23 of exact (9.1e-8 the largest seen; one fp32 fma: 2^-24, 6.0e-8);
+//    sums of more are closer than fp32 chains, since the hh products, exact in
+//    fp32, round into the main sum once per matrix instruction.
+//  * h can round up past x, so that hh overflows where x * y does not.
+// The kernels therefore take sums that are not finite again in fp32.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -325,3 +325,22 @@ def test_dense_tall_planes(sp, C, H, W, R):
     assert bool((out >= 0).all()) and bool(torch.isfinite(out).all())
     del x, out
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("C", [5, 40])
+@pytest.mark.parametrize("scale", [1e-32, 1e-34, 1e-35, 1e-36])
+def test_dense_small_values(sp, C, scale):
+    """Inputs of one magnitude down to 1e-36: below 2^-110 they count to the nearest
+    multiple of 2^-133, an error of at most 2^-134 for each factor of the filter;
+    above, relative errors are those of ordinary values."""
+    import torch
+    layer = synth.random_layer(8800 + C, 2, C, 40, 14, 14, 3, 3, 1, 1, 1.0, False, False, False, False)
+    x = ((layer.x + 0.5) * np.float32(scale)).astype(np.float32)
+    L = sp.SparseConvLayer(layer.w, None, None, 14, 14, 1, 1, False, False, path="dense")
+    say("dense small values", C, scale, L.plan(2))
+    out = L.run(torch.from_numpy(x).cuda())
+    torch.cuda.synchronize()
+    ref, ab = oracle.conv(x, layer.w, None, None, 1, 1, False, False)
+    _, wsum = oracle.conv(np.ones_like(x), layer.w, None, None, 1, 1, False, False)
+    lost = 2.0 ** -134 * wsum if scale < 2.0 ** -109 else 0.0
+    assert (np.abs(out.cpu().numpy() - ref) <= 1e-6 * ab + lost).all()

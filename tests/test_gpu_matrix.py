@@ -251,3 +251,28 @@ def test_input_without_a_finite_value(sp, i, value):
     for n in range(N):
         assert np.array_equal(out[n][~fin[0]], ref[0][~fin[0]], equal_nan=True)
         assert np.allclose(out[n][fin[0]], ref[0][fin[0]], rtol=1e-5, atol=1e-6)
+
+
+@pytest.mark.parametrize("side", ["inputs", "filter"])
+@pytest.mark.parametrize("scale", [1e-32, 1e-34, 1e-35, 1e-36])
+def test_small_values(sp, scale, side):
+    """Inputs or filter values of one magnitude down to 1e-36: below 2^-110 they
+    count to the nearest multiple of 2^-133, an error of at most 2^-134 for each
+    factor of the other side; above, relative errors are those of ordinary values."""
+    import torch
+    layer = synth.random_layer(9950, 2, 40, 40, 21, 23, 3, 3, 2, 1, 0.3, False, False, False, False)
+    x, w = layer.x + np.float32(0.5), layer.w + np.sign(layer.w) * np.float32(0.5)
+    if side == "inputs":
+        x = (x * np.float32(scale)).astype(np.float32)
+    else:
+        w = (w * np.float32(scale)).astype(np.float32)
+    L = sp.SparseConvLayer(w, layer.mask, None, 21, 23, 2, 1, False, False)
+    print("[case]", scale, side, L.plan(2), flush=True)
+    assert L.plan(2)["kernel"] == sp.SPCONV_KERNEL_MATRIX
+    out = L.forward_padded(L.pad_input(torch.from_numpy(x).cuda()))
+    torch.cuda.synchronize()
+    ref, ab = oracle.conv(x, w, layer.mask, None, 2, 1, False, False)
+    one = (np.ones_like(x), w) if side == "inputs" else (x, np.where(layer.mask, np.float32(1), np.float32(0)))
+    _, other = oracle.conv(*one, layer.mask, None, 2, 1, False, False)
+    lost = 2.0 ** -134 * other if scale < 2.0 ** -109 else 0.0
+    assert (np.abs(out.cpu().numpy() - ref) <= 1e-6 * ab + lost).all()
