@@ -194,8 +194,10 @@ def test_dense_extreme_values(sp):
         ab = torch.nn.functional.conv2d(torch.from_numpy(np.abs(layer.x)).double(),
                                         torch.from_numpy(np.abs(layer.w)).double(), padding=1).numpy()
     assert np.array_equal(np.isnan(got), np.isnan(ref))
-    assert np.array_equal(np.isinf(got) & (ab < 1e38), np.isinf(ref) & (ab < 1e38))
-    fin = np.isfinite(ref) & (ab < 3e38)
+    inf = np.isinf(ref)  # through an infinite input: float64 does not overflow here
+    assert (ref[inf] > 0).any() and (ref[inf] < 0).any() and np.array_equal(got[inf], ref[inf])
+    fin = np.isfinite(ref) & (ab < 3e38)  # (finite inputs may overflow fp32 beyond)
+    assert np.isfinite(got[fin]).all()
     assert (np.abs(got[fin] - ref[fin]) <= REL_TOL * ab[fin] + ABS_TOL).all()
 
 
@@ -221,12 +223,21 @@ def test_dense_tap_pairs(sp, C, H, W, pool):
     check_close(out.cpu().numpy(), ref, ab, f"tap pairs {C} {H}x{W}")
     assert np.array_equal(out.cpu().numpy().view(np.uint32), padded.cpu().numpy().view(np.uint32))
     conv = torch.nn.functional.conv2d(bad.cpu().double(), torch.from_numpy(layer.w).double(),
-                                      torch.from_numpy(layer.bias).double(), padding=1)
-    if not pool:
-        got, want = raw.cpu().double(), conv
-        assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(torch.isinf(got), torch.isinf(want))
-        same = torch.isfinite(want)
-        assert torch.equal(got[same], out.cpu().double()[same])
+                                      torch.from_numpy(layer.bias).double(), padding=1).numpy()
+    touched = ~np.isfinite(conv)
+    got, want, clean = raw.cpu().double().numpy(), conv, out.cpu().double().numpy()
+    if pool:  # a window's maximum skips NaN, unless all four are
+        def corners(t):
+            t = t[:, :, :H // 2 * 2, :W // 2 * 2]
+            return [t[:, :, i::2, j::2] for i in (0, 1) for j in (0, 1)]
+        want = np.fmax.reduce(corners(conv))
+        touched = np.logical_or.reduce(corners(touched))
+    assert np.isinf(want).any()
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    assert np.array_equal(got[~touched], clean[~touched])
+    some = touched & np.isfinite(want)
+    assert np.allclose(got[some], want[some], rtol=1e-5, atol=1e-5)
 
 
 def test_dense_more_images_than_one_launch_counts(sp):
