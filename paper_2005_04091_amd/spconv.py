@@ -133,14 +133,16 @@ def spconv_strerror(code: int) -> str:
     return _lib.spconv_strerror(int(code)).decode()
 
 
-# A function of its integers alone, asked several times per forward call (typed: a
-# float that equals a remembered integer is refused as ever).
-@lru_cache(maxsize=1024, typed=True)
 def spconv_output_shape(H, W, R, S, stride, pad, flags):
     ho, wo = _c_int(), _c_int()
     _check(_lib.spconv_output_shape(H, W, R, S, stride, pad, flags, ctypes.byref(ho), ctypes.byref(wo)),
            "spconv_output_shape")
     return ho.value, wo.value
+
+
+# For the forward calls, which ask it several times: a function of its integers
+# alone. (It takes 14.0 for a remembered 14, as the call that follows does not.)
+_output_shape = lru_cache(maxsize=1024)(spconv_output_shape)
 
 
 @dataclass
@@ -362,7 +364,7 @@ def spconv_forward(xp, N: int, C: int, H: int, W: int, csr: DeviceCSR, K: int, R
     """Fused sparse conv + bias + ReLU (+ 2x2 max-pool) on the padded input
     ``xp``: the plain ``spconv_forward`` call (no options, so the planner does
     not see ``csr``'s row skew)."""
-    Ho, Wo = spconv_output_shape(H, W, R, S, stride, pad, flags)
+    Ho, Wo = _output_shape(H, W, R, S, stride, pad, flags)
     s, out = _stream_and_out(stream, xp.device, out, (N, K, Ho, Wo))
     _check_numel(xp, _in_elems(N, C, H, W, pad, flags), "xp")
     _check_numel(out, N * K * Ho * Wo, "out")
@@ -383,9 +385,9 @@ def spconv_forward_ex(xp, N: int, C: int, H: int, W: int, csr: DeviceCSR, K: int
     on ``csr``'s host arrays; 0 = unknown), and ``lowered`` (a device int32
     tensor from ``spconv_pack_lowered`` for this call) feeds the stride-1
     kernel its entries ready-made."""
-    Hs, Ws = spconv_output_shape(H, W, R, S, stride, pad, flags)
+    Hs, Ws = _output_shape(H, W, R, S, stride, pad, flags)
     s, out = _stream_and_out(stream, xp.device, out, (N, K, Hs + 2 * out_pad, Ws + 2 * out_pad))
-    Hc, Wc = spconv_output_shape(H, W, R, S, stride, pad, flags & ~SPCONV_MAXPOOL2X2)
+    Hc, Wc = _output_shape(H, W, R, S, stride, pad, flags & ~SPCONV_MAXPOOL2X2)
     _check_numel(xp, _in_elems(N, C, H, W, pad, flags), "xp")
     _check_numel(out, N * K * (Hs + 2 * out_pad) * (Ws + 2 * out_pad), "out")
     _check_numel(bias, K, "bias")
@@ -411,9 +413,9 @@ def spconv_forward_dense(xp, N: int, C: int, H: int, W: int, packed, K: int, R: 
                          stream=None):
     """The fused conv of ``spconv_forward_ex`` from the packed dense filter
     ``packed`` (device), stride 1."""
-    Hs, Ws = spconv_output_shape(H, W, R, S, 1, pad, flags)
+    Hs, Ws = _output_shape(H, W, R, S, 1, pad, flags)
     s, out = _stream_and_out(stream, xp.device, out, (N, K, Hs + 2 * out_pad, Ws + 2 * out_pad))
-    Hc, Wc = spconv_output_shape(H, W, R, S, 1, pad, flags & ~SPCONV_MAXPOOL2X2)
+    Hc, Wc = _output_shape(H, W, R, S, 1, pad, flags & ~SPCONV_MAXPOOL2X2)
     _check_numel(xp, _in_elems(N, C, H, W, pad, flags), "xp")
     _check_numel(packed, spconv_dense_size(K, C, R, S), "packed")
     _check_numel(out, N * K * (Hs + 2 * out_pad) * (Ws + 2 * out_pad), "out")

@@ -46,3 +46,12 @@ def test_output_shape_refuses_floats_it_has_answered_as_integers(sp):
     for args in [(14.0, 14, 3, 3, 1, 1, 1), (14, 14, 3, 3, 1.0, 1, 1), (14, 14, 3, 3, 1, 1, 1.0)]:
         with pytest.raises(ctypes.ArgumentError):
             sp.spconv_output_shape(*args)
+
+
+def test_forward_refuses_floats_for_remembered_sizes(sp):
+    """The forward calls remember output shapes by value, and 14.0 equals 14: the
+    library call refuses it (nothing is queued: the buffers are NULL too)."""
+    assert sp._output_shape(14, 14, 3, 3, 1, 1, 1) == sp._output_shape(14.0, 14, 3, 3, 1, 1, 1)
+    csr = sp.spconv_csr(4, 4, 3, 3, 16, 16, 0, None, None, None, None)
+    with pytest.raises(ctypes.ArgumentError):
+        sp._lib.spconv_forward_ex(None, 1, 4, 14.0, 14, ctypes.byref(csr), 4, 3, 3, 1, 1, None, 1, None, None, None)
