@@ -445,11 +445,18 @@ int spconv_dense_plan(int N, int C, int H, int W, int K, int R, int S, int pad, 
 /*
  * spconv_select_path - which path is predicted faster for this layer on
  * MI355X (host only): SPCONV_PATH_DENSE when the dense kernel applies (stride
- * 1, 3x3 or 1x1, a plan exists) and the filter density nnz / (K*C*R*S) is
- * above the break-even density measured on MI355X for the output's size
- * (0.24 at 14x14, 0.43 at 56x56, log-linear in Ho*Wo between and beyond,
- * clamped to [0.2, 0.5]; the paper's CPU figure is 43.5%); otherwise
- * SPCONV_PATH_SPARSE.
+ * 1, 3x3 or 1x1, a plan exists) and its modelled time is below the sparse path's
+ * (the stride-1 or the matrix kernel, whichever spconv_plan reports); otherwise
+ * SPCONV_PATH_SPARSE. Without SPCONV_UNPADDED_INPUT both are for an input that has
+ * its border; with it the stride-1 kernel's time includes a pad pass where W is
+ * not a multiple of 4. The models are fitted to measurements over 7x7 to 224x224
+ * planes, batches 1 to 32 and densities 0.03 to 1 (by themselves they miss the
+ * faster path by 0.5 % of its time on average). The break-even density they give
+ * depends on the layer: 0.19 for 256 channels at 14x14 in a batch of 32 and 0.55 for one image,
+ * 0.31 for 64 channels at 56x56 (the paper's CPU figure is 43.5%). Filters of
+ * more than 0.245 (up to 14x14) to 0.67 (from 224x224) of all taps take the dense
+ * path in any case where the other choice is the stride-1 kernel, whose sums are
+ * less close.
  * Errors: SPCONV_EINVAL for a NULL path, sizes < 1, stride < 1, pad < 0, nnz
  * outside [0, K*C*R*S], unknown flags.
  */

@@ -40,6 +40,10 @@
 #include "spconv.h"
 
 __attribute__((visibility("hidden"))) int dense_kernel_variants(int32_t *variants, int32_t capacity, int32_t *count);
+// Modelled time of the sparse path (spconv.hip).
+__attribute__((visibility("hidden"))) bool sparse_layer_us(int N, int C, int H, int W, int K, int R, int S, int pad,
+                                                           int Ho, int Wo, bool pool, bool unpadded, long long nnz,
+                                                           double *us, bool *walk);
 
 namespace {
 
@@ -52,6 +56,7 @@ constexpr int kDnsWaveBlocks = 4;         // pixel blocks per wave (16 accumulat
 constexpr int kDnsGroup = 16;             // channels per MFMA (one reduction group)
 constexpr int kDnsPxBytes = 6 * kDnsGroup;  // LDS bytes of a group's pixel: three bf16 parts of 16 channels
 constexpr int kDnsLdsBytes = 64 * 1024;   // per workgroup: two resident per CU
+constexpr int kDnsCuLds = 160 * 1024;     // LDS of a CU
 constexpr int kDnsLdsMax = 80 * 1024;     // one group of the widest rows (256 padded columns, 3 rows)
 constexpr int kDnsPoolCh = 8;             // channels of one pooled staging round (4 accumulator rows x 2 halves)
 constexpr int kDnsRounds = 3;             // staging tasks per thread whose loads run a chunk ahead
@@ -861,16 +866,39 @@ extern "C" int spconv_dense_plan(int N, int C, int H, int W, int K, int R, int S
 
 namespace {
 
-// Break-even filter density on MI355X: above it the dense kernel beats the
-// sparse ones. Measured with both paths on the same layers (fp32, batch 32,
-// back-to-back launches): about 0.245 for 256 channels at 14x14, 0.44 for 128
-// channels at 28x28 with the pool, 0.42-0.47 at 56x56 (64 or 128 channels,
-// pooled or not) and 0.67 for 64 channels at 224x224. The sparse kernels spread
-// each entry's fixed cost over the pixels of an image tile, so their rate,
-// and the break-even, grow with the image: the threshold interpolates
-// log-linearly in output pixels per image between those measurements and
-// stays at the end values beyond them.
-double break_even_density(int Ho, int Wo) {
+// Microseconds of the dense kernel on a plan: per round of workgroups (one or two a
+// CU) 7.2, the MFMAs of a SIMD's waves at 59 % of their rate, and 0.55 for each
+// round of staging loads past those that run a chunk ahead; the bytes of the planes
+// and of the filter; and the input's that the 256 MB of Infinity Cache do not
+// hold, which neighbouring tiles fetch again. Against 422 layers (those of
+// sparse_layer_us) half are within 7 % and nine in ten within 20 %.
+double dense_us(const DensePlan &pl, const DenseArgs &a, int R, int S) {
+    const int waves = pl.nw * pl.ksr * pl.ksp;
+    const int ngroups = (a.C + kDnsGroup - 1) / kDnsGroup;
+    const bool pairs = dense_pairs(a.C, R, S);
+    const int resident = std::max(1, std::min(8 / waves, kDnsCuLds / (int)pl.lds_bytes));
+    const double rounds = std::ceil(pl.total_wgs / (256.0 * resident));
+    const double per_simd = std::max(1.0, std::min((double)resident, std::ceil(pl.total_wgs / 256.0)) * waves / 4.0);
+    const int steps = (ngroups + pl.ksr - 1) / pl.ksr * (pairs ? (R * S + 1) / 2 : R * S);
+    const double mfma = 6.0 * 32.0 * steps * pl.NBW * per_simd;
+    const int tasks = (pairs ? 1 : 2 * std::min(pl.Cg, ngroups)) * pl.PX;
+    const int threads = waves * kWave;
+    const double late = std::max(0, (tasks + threads - 1) / threads - kDnsRounds) * (double)pl.nchunks;
+    const double in = 4e-6 * a.N * ((double)a.C * a.Hp * a.Wp), out = 4e-6 * a.N * ((double)a.K * a.Hq * a.Wq);
+    const double filter = 4e-6 * round_up(a.K, kDnsTile) * (double)a.C * R * S;
+    return rounds * (7.2 + 0.704e-3 * mfma + 0.55 * late) + 0.33 * (in + out) + 1.9 * std::max(0.0, in - 256.0) +
+           0.94 * filter;
+}
+
+// Filter density from which a layer stays dense where the other choice is the
+// stride-1 walk, also if that is modelled faster: the dense sums are closer, 1.05 to
+// 2.4 times and half of them 1.5 times, than the walk's chains of fp32 products
+// (against float64 on 42 layers of densities 0.26 to 0.7), and layers this dense
+// have always had them. (The line is where the fp32 MFMA kernel before this one
+// broke even: 14x14, 28x28, 56x56 and 224x224 in batches of 32, log-linear in
+// output pixels between.) What it costs: 3 to 16 channels, above all, 3 channels at
+// 224x224 in a batch of 32 298 against 159 us.
+double kept_dense_density(int Ho, int Wo) {
     struct Anchor {
         double px, d;
     };
@@ -899,6 +927,12 @@ extern "C" int spconv_select_path(int N, int C, int H, int W, int K, int R, int 
     DenseArgs a;
     if (prepare_dense(N, C, H, W, K, R, S, pad, flags & ~SPCONV_UNPADDED_INPUT, nullptr, &pl, &a) != SPCONV_OK)
         return SPCONV_OK;
-    if ((double)nnz > break_even_density(a.Ho, a.Wo) * (double)K * C * R * S) *path = SPCONV_PATH_DENSE;
+    double sparse;
+    bool walk;
+    if (!sparse_layer_us(N, C, H, W, K, R, S, pad, a.Ho, a.Wo, (flags & SPCONV_MAXPOOL2X2) != 0,
+                         (flags & SPCONV_UNPADDED_INPUT) != 0, nnz, &sparse, &walk) ||
+        dense_us(pl, a, R, S) < sparse ||
+        (walk && (double)nnz > kept_dense_density(a.Ho, a.Wo) * (double)K * C * R * S))
+        *path = SPCONV_PATH_DENSE;
     return SPCONV_OK;
 }

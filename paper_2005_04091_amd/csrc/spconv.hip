@@ -2175,6 +2175,12 @@ extern "C" int spconv_resize_pad_input(const float *in, int N, int C, int Hin, i
 
 namespace {
 
+// Modelled microseconds of the stride-1 kernel and of the matrix kernel on a plan
+// (within about 10 % on 44 layers of 7x7 to 224x224, 32 to 512 channels, batch 1 to
+// 32, 1x1 to 5x5, densities 0.05 to 0.6).
+double walk_us(const Plan &pl) { return 7.5 + 0.27e-3 * pl.time; }
+double matrix_us(const MatrixPlan &mp) { return 5.0 + 0.5e-3 * mp.time; }
+
 // Whether a call without a lowered stream runs on the matrix cores (matrix.hip).
 //
 // Strided layers of at least one whole octet of input channels: measured from
@@ -2200,10 +2206,39 @@ namespace {
 bool use_matrix(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, bool pool, long long nnz,
                 const Plan &pl, MatrixPlan *mp) {  // C >= 8
     if (stride != 1) return matrix_plan(N, C, H, W, K, R, S, stride, pad, pool, nnz, mp);
-    const double walk_us = 7.5 + 0.27e-3 * pl.time;
-    if ((long long)H * W < 49 || walk_us < 15.0 || !matrix_plan(N, C, H, W, K, R, S, stride, pad, pool, nnz, mp)) return false;
-    return walk_us > 1.15 * (5.0 + 0.5e-3 * mp->time);
+    const double walk = walk_us(pl);
+    if ((long long)H * W < 49 || walk < 15.0 || !matrix_plan(N, C, H, W, K, R, S, stride, pad, pool, nnz, mp)) return false;
+    return walk > 1.15 * matrix_us(*mp);
 }
+
+}  // namespace
+
+// Microseconds of a stride-1 layer on the sparse path (the stride-1 kernel or the
+// matrix kernel, as use_matrix chooses; *walk: the former), for spconv_select_path;
+// false when it has no plan. Beside the planners' cycles, which order tilings, these count the
+// planes' bytes and the filter's entries: against 3700 measurements (layers of 7x7
+// to 224x224, 3 to 512 channels, batch 1 to 32, 1x1 and 3x3, densities 0.03 to 1)
+// half are within 6 % and nine in ten within 17 %. The stride-1 kernel forms the
+// border of an unpadded input at the price of a pad pass, a launch and the bytes,
+// where the rows are no whole 16-byte groups.
+__attribute__((visibility("hidden"))) bool sparse_layer_us(int N, int C, int H, int W, int K, int R, int S, int pad,
+                                                           int Ho, int Wo, bool pool, bool unpadded, long long nnz,
+                                                           double *us, bool *walk) {
+    Plan pl;
+    MatrixPlan mp;
+    const int Hp = H + 2 * pad, Wp = W + 2 * pad;
+    if (!plan_stride1(N, C, K, Hp, Wp, Wp, 0, Ho, Wo, R, S, pool, nnz, 0, false, &pl)) return false;
+    const double stored = pool ? (double)(Ho / 2) * (Wo / 2) : (double)Ho * Wo;
+    const double in = 4e-6 * N * ((double)C * Hp * Wp), mb = in + 4e-6 * N * (K * stored), entries = 1e-6 * (double)nnz;
+    *walk = C < 8 || !use_matrix(N, C, H, W, K, R, S, 1, pad, pool, nnz, pl, &mp);
+    if (!*walk)
+        *us = 1.6 + 0.545e-3 * mp.time + 0.06 * mb + 17.5 * entries;
+    else
+        *us = 4.8 + 0.26e-3 * pl.time + 0.21 * mb + 59.0 * entries + (unpadded && W % 4 ? 2.9 + 0.26 * in : 0.0);
+    return true;
+}
+
+namespace {
 
 // Host-side checks of a forward call (everything but the buffer pointers) and
 // its launch plan. Returns SPCONV_OK or SPCONV_EINVAL. With `mp` the call may run

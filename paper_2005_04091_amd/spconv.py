@@ -488,7 +488,7 @@ class SparseConvLayer:
             if N is None:
                 raise ValueError('path="auto" needs the batch size N')
             sel = spconv_select_path(N, self.C, H, W, self.K, self.R, self.S, stride, pad, self.host_csr.nnz,
-                                     self.flags)
+                                     self.flags | SPCONV_UNPADDED_INPUT)  # as forward takes it
             path = "dense" if sel == SPCONV_PATH_DENSE else "sparse"
         if path not in ("sparse", "dense"):
             raise ValueError(f"unknown path {path!r}")

@@ -107,6 +107,55 @@ def test_dense_plans_cover_the_tile_shapes(sp):
     assert p["tile_rows"] % 2 == 0
 
 
+# N, C, K, H = W, R, flags; the dense kernel's measured time (us, padded input, graph
+# replay); densities measured with the sparse path's time, each at least a tenth
+# from the dense one.
+MEASURED = [
+    ((32, 512, 512, 7, 3, 1), 118, {0.08: 64, 0.24: 153}),
+    ((1, 256, 256, 14, 3, 1), 28, {0.24: 22, 0.65: 33}),
+    ((8, 256, 256, 14, 3, 1), 34, {0.13: 25, 0.38: 38}),
+    ((32, 256, 256, 14, 3, 1), 59, {0.13: 44, 0.24: 68}),
+    ((1, 128, 128, 28, 3, 3), 26, {0.08: 13, 0.55: 21}),
+    ((8, 128, 128, 28, 3, 1), 22, {0.13: 17, 0.38: 32}),
+    ((32, 128, 128, 28, 3, 3), 52, {0.13: 37, 0.3: 65}),
+    ((8, 128, 128, 56, 3, 1), 57, {0.18: 47, 0.3: 67}),
+    ((32, 64, 64, 56, 3, 1), 66, {0.24: 52, 0.8: 76}),
+    ((32, 64, 64, 112, 3, 1), 260, {0.3: 214, 1.0: 292}),
+    ((32, 64, 64, 224, 3, 1), 1231, {0.2: 635, 0.55: 1043}),
+    ((8, 3, 64, 112, 3, 1), 26, {0.24: 14}),
+    ((32, 3, 64, 224, 3, 1), 298, {0.24: 140, 0.65: 159}),
+    ((32, 256, 256, 14, 1, 1), 18, {0.08: 15, 0.3: 21}),
+    ((32, 64, 256, 28, 1, 1), 27, {0.3: 23, 0.8: 30}),
+]
+
+
+@pytest.mark.parametrize("layer,dense,sparse", MEASURED)
+def test_select_path_picks_the_measured_faster_one(sp, layer, dense, sparse):
+    N, C, K, H, R, flags = layer
+    for d, us in sparse.items():
+        want = sp.SPCONV_PATH_SPARSE if us < dense else sp.SPCONV_PATH_DENSE
+        assert sp.spconv_select_path(N, C, H, H, K, R, R, 1, R // 2, int(d * K * C * R * R), flags) == want, d
+
+
+@pytest.mark.parametrize("N,C,H,line", [(32, 3, 224, 0.67), (8, 3, 112, 0.55), (4, 3, 14, 0.245)])
+def test_select_path_keeps_dense_filters_from_the_walk(sp, N, C, H, line):
+    """The walk is faster at any density on 3 channels; above the line the dense
+    kernel's closer sums are kept."""
+    sel = lambda d: sp.spconv_select_path(N, C, H, H, 64, 3, 3, 1, 1, int(d * 64 * C * 9), 1)
+    assert sel(line - 0.02) == sp.SPCONV_PATH_SPARSE and sel(line + 0.02) == sp.SPCONV_PATH_DENSE
+
+
+@pytest.mark.parametrize("W,same", [(14, False), (16, True)])
+def test_select_path_counts_the_pad_pass_of_an_unpadded_input(sp, W, same):
+    """256 channels, batch 32: a pad pass of 4.8 us at 14x14 moves the break-even
+    down; rows of whole 16-byte groups need none."""
+    def break_even(flags):
+        return next(i for i in range(100) if sp.spconv_select_path(
+            32, 256, W, W, 256, 3, 3, 1, 1, int(i / 100 * 256 * 256 * 9), flags) == sp.SPCONV_PATH_DENSE)
+    padded, unpadded = break_even(1), break_even(1 | sp.SPCONV_UNPADDED_INPUT)
+    assert unpadded == padded if same else 0.12 < unpadded / 100 < padded / 100 < 0.24
+
+
 def test_select_path(sp):
     sel = sp.spconv_select_path
     full = 256 * 256 * 9
@@ -116,18 +165,8 @@ def test_select_path(sp):
     assert sel(32, 256, 14, 14, 256, 3, 3, 2, 1, full, 1) == sp.SPCONV_PATH_SPARSE   # stride 2: sparse only
     assert sel(32, 64, 14, 14, 64, 5, 5, 1, 2, 64 * 64 * 25, 1) == sp.SPCONV_PATH_SPARSE  # no 5x5 dense kernel
     assert sel(32, 64, 56, 56, 64, 3, 3, 1, 1, 0, 1) == sp.SPCONV_PATH_SPARSE
-    # measured break-even: 0.43 at 56x56, 0.245 at 14x14, 0.44 at 28x28 (pooled), 0.67 at 224x224
-    assert sel(32, 64, 56, 56, 64, 3, 3, 1, 1, int(0.42 * 64 * 64 * 9), 1) == sp.SPCONV_PATH_SPARSE
-    assert sel(32, 64, 56, 56, 64, 3, 3, 1, 1, int(0.44 * 64 * 64 * 9), 1) == sp.SPCONV_PATH_DENSE
-    assert sel(32, 256, 14, 14, 256, 3, 3, 1, 1, int(0.23 * full), 1) == sp.SPCONV_PATH_SPARSE
-    assert sel(32, 256, 14, 14, 256, 3, 3, 1, 1, int(0.25 * full), 1) == sp.SPCONV_PATH_DENSE
-    c128 = 128 * 128 * 9
-    assert sel(32, 128, 28, 28, 128, 3, 3, 1, 1, int(0.42 * c128), 3) == sp.SPCONV_PATH_SPARSE
-    assert sel(32, 128, 28, 28, 128, 3, 3, 1, 1, int(0.46 * c128), 3) == sp.SPCONV_PATH_DENSE
-    c64 = 64 * 64 * 9
-    assert sel(32, 64, 224, 224, 64, 3, 3, 1, 1, int(0.65 * c64), 1) == sp.SPCONV_PATH_SPARSE
-    assert sel(32, 64, 224, 224, 64, 3, 3, 1, 1, int(0.69 * c64), 1) == sp.SPCONV_PATH_DENSE
     assert sel(32, 64, 224, 224, 64, 3, 3, 1, 1, 64 * 64 * 9, 3) == sp.SPCONV_PATH_SPARSE  # pooled 226-wide rows: no dense plan
+    assert sel(32, 64, 56, 56, 64, 3, 3, 1, 1, int(0.42 * 64 * 64 * 9), 1) == sp.SPCONV_PATH_DENSE
     lib, E, out = sp._lib, sp.SPCONV_EINVAL, ctypes.c_int()
     assert lib.spconv_select_path(32, 64, 56, 56, 64, 3, 3, 1, 1, 7280, 1, None) == E
     assert lib.spconv_select_path(32, 64, 56, 56, 64, 3, 3, 1, 1, -1, 1, ctypes.byref(out)) == E
