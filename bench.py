@@ -90,7 +90,16 @@ def algorithmic(layer, nnz):
 KERNEL_SOURCES = {
     "fwd": [ROOT / "paper_2005_04091_amd" / "csrc" / f for f in ("spconv.hip", "common.h")],
     "dense": [ROOT / "paper_2005_04091_amd" / "csrc" / f for f in ("dense.hip", "split.h", "common.h")],
+    "matrix": [ROOT / "paper_2005_04091_amd" / "csrc" / f for f in ("matrix.hip", "matrix.h", "split.h", "common.h")],
 }
+
+
+def kernel_family(L, N: int) -> str:
+    """The family whose kernel a layer's forward of batch N runs."""
+    from paper_2005_04091_amd import spconv
+    if L.path == "dense":
+        return "dense"
+    return "matrix" if L.plan(N)["kernel"] == spconv.SPCONV_KERNEL_MATRIX else "fwd"
 
 
 def kernel_source_sha(family: str = "fwd") -> str:
@@ -446,8 +455,9 @@ def per_config_record(name, args, dev, stream):
     """One of the other layer configurations, measured like the block's layers:
     back-to-back launches (warm), the cold median of 30 of the forward alone and
     of pad + forward, nonzero GFLOP/s, and the roofline figures against HBM and
-    the arithmetic peak of the path that runs (v_fma_f32 for the sparse kernels,
-    fp32 products as six bf16 part products on the matrix cores for the dense one)."""
+    the arithmetic peak of the kernel that runs (v_fma_f32 for the walk, fp32
+    products as six bf16 part products on the matrix cores for the dense and the
+    matrix kernel, which multiply every tap)."""
     import torch
     from paper_2005_04091_amd import spconv, synth
     layer = synth.make_layer(name)
@@ -482,9 +492,12 @@ def per_config_record(name, args, dev, stream):
            "nonzero_gflops": round(flops / (ms_cold * 1e-3) / 1e9, 1),
            "nonzero_gflops_warm": round(flops / (ms_warm * 1e-3) / 1e9, 1),
            "algorithmic_bytes": int(nbytes), "nonzero_flops": flops}
-    if L.path == "dense":
-        dflops = 2.0 * K * C * R * S * N * L.Ho * L.Wo
-        nbytes_d = nbytes + 4.0 * L.dense.numel() - 8.0 * nnz
+    family = kernel_family(L, N)
+    if family != "fwd":
+        # (the convolution's pixels: a pooled layer stores a quarter of them)
+        dflops = 2.0 * K * C * R * S * N * ((H + 2 * layer.pad - R) // layer.stride + 1) * (
+            (W + 2 * layer.pad - S) // layer.stride + 1)
+        nbytes_d = nbytes + (4.0 * L.dense.numel() - 8.0 * nnz if family == "dense" else 0.0)
         rec["roof"] = roof(dflops, nbytes_d, ms_cold, MFMA_SPLIT_FP32_TFLOPS)
         rec["roof"]["flops_counted"] = "dense filter work, six bf16 part products per fp32 product"
         rec["nonzero_flops_roof"] = roof(flops, nbytes, ms_cold, VALU_FP32_FMA_TFLOPS)
@@ -759,7 +772,7 @@ def main():
     L = spconv.SparseConvLayer(layer.w, layer.mask, layer.bias, H, W, layer.stride, layer.pad, layer.relu,
                                layer.pool, device=dev, path=args.path, N=N)
     nnz = L.host_csr.nnz
-    dense = L.path == "dense"
+    family = kernel_family(L, N)
     print(f"[bench] path {L.path}: {L.plan(N, unpadded=L.pads_in_kernel(N))}", file=sys.stderr, flush=True)
     x = torch.from_numpy(layer.x).to(dev)
     xp = torch.empty((N, C, H + 2 * layer.pad, W + 2 * layer.pad), dtype=torch.float32, device=dev)
@@ -820,13 +833,15 @@ def main():
     if fused_pad:  # the kernel reads the unpadded input
         fwd_bytes -= 4.0 * N * C * ((H + 2 * layer.pad) * (W + 2 * layer.pad) - H * W)
     value = flops / (ms_per_step * 1e-3) / 1e9
-    if dense:
-        # The dense kernel's algorithmic work is every filter tap (its FLOPs on
-        # the stored pixels), as bf16 part products; its filter read is the
-        # packed dense array instead of the CSR.
-        kern_flops = 2.0 * K * C * R * S * N * (H + 2 * layer.pad - R + 1) * (W + 2 * layer.pad - S + 1)
-        fwd_bytes += 4.0 * L.dense.numel() - (8.0 * nnz)
-        bound, peak, kname = "mfma", MFMA_SPLIT_FP32_TFLOPS, "spconv_dense_kernel"
+    if family != "fwd":
+        # The algorithmic work of the dense and matrix kernels is every filter tap
+        # (its FLOPs on the convolution's pixels), as bf16 part products; the dense
+        # one reads the packed filter instead of the CSR.
+        kern_flops = 2.0 * K * C * R * S * N * ((H + 2 * layer.pad - R) // layer.stride + 1) * (
+            (W + 2 * layer.pad - S) // layer.stride + 1)
+        if family == "dense":
+            fwd_bytes += 4.0 * L.dense.numel() - (8.0 * nnz)
+        bound, peak, kname = "mfma", MFMA_SPLIT_FP32_TFLOPS, f"spconv_{family}_kernel"
     else:
         kern_flops = flops
         bound, peak, kname = "alu", VALU_FP32_FMA_TFLOPS, "spconv_fwd_kernel"
@@ -864,7 +879,7 @@ def main():
             "peak": peak,
             "unit": "TFLOP/s",
             "frac": round(achieved_tflops / peak, 4),
-            "traffic": measured_traffic(args.workload, "dense" if dense else "fwd"),
+            "traffic": measured_traffic(args.workload, family),
             "algorithmic_bytes": int(fwd_bytes),
             "flops": kern_flops,
         },
