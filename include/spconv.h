@@ -45,7 +45,8 @@ extern "C" {
 /* The input is the unpadded [N][C][H][W] tensor: the kernel forms the zero
  * border itself while staging the input in LDS, so no padded copy is made
  * (the pad step fused into the convolution). Stride-1 layers and the dense
- * path only: a strided layer gets SPCONV_EINVAL. The results are bit-identical to the padded input's. */
+ * path only: a strided layer gets SPCONV_EINVAL. The results are bit-identical to
+ * the padded input's. */
 #define SPCONV_UNPADDED_INPUT 4u
 
 /*
@@ -159,8 +160,7 @@ int spconv_resize_pad_input(const float *in, int N, int C, int Hin, int Win, int
  * are reproducible run to run for a given device and shape).
  * Errors: SPCONV_EINVAL (NULL pointer, sizes < 1, stride < 1, pad < 0, shape
  * mismatch with csr, nnz outside [0, 2^31),
- * unknown flag bits, SPCONV_UNPADDED_INPUT with a plan other than the
- * stride-1 kernel, empty output,
+ * unknown flag bits, SPCONV_UNPADDED_INPUT with a stride other than 1, empty output,
  * Ho or Wo < 2 with the pool flag, C*Hp*Wp >= 2^31); SPCONV_EHIP when the
  * launch fails.
  */
@@ -204,8 +204,8 @@ int spconv_forward(const float *in_padded, int N, int C, int H, int W, const spc
  *           decoding the CSR rows itself (the bits of its own walk of them; a
  *           call without a stream may take SPCONV_KERNEL_MATRIX instead, which
  *           sums in another order);
- *           csr->offset and csr->vals are then not read. Calls whose plan is
- *           not the stride-1 kernel get SPCONV_EINVAL.
+ *           csr->offset and csr->vals are then not read. Calls of another
+ *           stride get SPCONV_EINVAL.
  * lowered_words  number of int32 words of `lowered`; must equal
  *           spconv_lowered_size for the call (SPCONV_EINVAL otherwise).
  * Both borders are limited so that one padded plane has fewer than 2^31
@@ -266,8 +266,7 @@ int spconv_forward_ex(const float *in_padded, int N, int C, int H, int W, const 
  * with these arguments (host only; csr's arrays are not read):
  *   4 * tiles * 16 * channels_per_wave * chunks + 2 * (nnz + 16).
  * Errors: those of spconv_forward_ex's argument checks (opt->lowered is not
- * looked at); SPCONV_EINVAL for a NULL words or a plan other than the
- * stride-1 kernel.
+ * looked at); SPCONV_EINVAL for a NULL words or a stride other than 1.
  */
 int spconv_lowered_size(int N, int C, int H, int W, const spconv_csr *csr, int K, int R, int S, int stride, int pad,
                         uint32_t flags, const spconv_options *opt, int64_t *words);

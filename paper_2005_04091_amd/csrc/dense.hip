@@ -22,7 +22,7 @@
 //    [8 bf16], so a B fragment (8 channels of a pixel shifted by the tap) is
 //    one 16-byte LDS read per part, consecutive over the lanes;
 //  * the A fragment of (group, tap) is four 8-byte loads from the filter
-//    packed by spconv_pack_dense, two steps ahead, split in registers;
+//    packed by spconv_pack_dense, three steps ahead, split in registers;
 //  * the epilogue adds bias (and a residual), applies ReLU, pools 2x2 windows
 //    through LDS when asked, and stores once. Sums that are not finite are taken
 //    again on the fp32 MFMA: infinities (and values that round to one in bf16)
@@ -55,7 +55,7 @@ constexpr int kDnsMaxBlocks = 8;          // pixel blocks per tile
 constexpr int kDnsWaveBlocks = 4;         // pixel blocks per wave (16 accumulator VGPRs each)
 constexpr int kDnsGroup = 16;             // channels per MFMA (one reduction group)
 constexpr int kDnsPxBytes = 6 * kDnsGroup;  // LDS bytes of a group's pixel: three bf16 parts of 16 channels
-constexpr int kDnsLdsBytes = 64 * 1024;   // per workgroup: two resident per CU
+constexpr int kDnsLdsBytes = 64 * 1024;   // per workgroup: two fit a CU, where their registers do (at most four waves each)
 constexpr int kDnsCuLds = 160 * 1024;     // LDS of a CU
 constexpr int kDnsLdsMax = 80 * 1024;     // one group of the widest rows (256 padded columns, 3 rows)
 constexpr int kDnsPoolCh = 8;             // channels of one pooled staging round (4 accumulator rows x 2 halves)
@@ -150,20 +150,28 @@ __device__ __forceinline__ void dense_put(const DenseArgs &a, char *buf, const S
 // What bounds it: at 14x14 (256 channels, batch 32, one workgroup per CU) the
 // MFMAs alone take about 33 us (the chip holds 1.65 PFLOP/s on this MFMA form)
 // and everything else (the A loads and their split, LDS reads, staging) about
-// 35 us without them; together 54 us, where the fp32 MFMA kernel this replaces
-// took 88 us. Other layers, batch 32, before and after: 56x56, 64 channels 98
-// -> 68 us; 28x28, 128 channels, pooled 82 -> 51 us; 7x7, 512 channels 171 ->
-// 110 us; 112x112, 64 channels (batch 8) 97 -> 83 us. Against float64 the sums
-// are two to three times closer than that kernel's (14x14: 1.5e-7 against
-// 4.1e-7 relative), because the hh products round into the main sum once per
-// 16 channels and tap. Chunks of 32 to 96 channels take the same time.
+// 35 us without them; together 56 us, where the fp32 MFMA kernel before it
+// took 88 us. Other layers, batch 32, fp32 MFMA kernel and this one: 56x56, 64
+// channels 98 and 63 us; 28x28, 128 channels, pooled 82 and 52 us; 7x7, 512
+// channels 171 and 112 us; 112x112, 64 channels (batch 8) 97 and 76 us. Against
+// float64 the sums are two to three times closer than that kernel's (14x14: 1.5e-7
+// against 4.1e-7 relative), because the hh products round into the main sum once
+// per 16 channels and tap. Chunks of 32 to 96 channels take the same time.
+//
+// Registers: 191 to 256 (tap pairs 138 to 256), so two waves a SIMD. With four
+// blocks a wave they do not suffice: 42 to 52 are spilled (3x3; 19 with three
+// blocks, 8 for 1x1, 13 for tap pairs), mostly the next chunk's loads: some 30
+// scratch stores before a chunk's MFMAs and as many loads after them, 6 loads to a
+// group's 216 MFMAs, none between these. Tiles of at most three blocks a wave took
+// 68 us for the 56x56 layer's 63, and 65 for the 112x112 one's 76; the planner does
+// not tell them apart yet.
 //
 // PAIR (filters of several taps, at most 8 channels): the second half of an
 // MFMA's 16 channels would be padding, so it takes the next tap instead, 5 MFMA
 // steps for 3x3 where there were 9, and only one octet is staged.
-// 3x3 on 3 channels, 64 outputs, 224x224 batch 32: 396 -> 321 us (fp32 MFMA
-// kernel 374); 56x56 batch 8 10.8 us (14.4); 8 channels at 112x112, batch 4,
-// 16.6 us (32.8). The output's stores are most of what is left.
+// 3x3 on 3 channels, 64 outputs, 224x224 batch 32: 297 us (396 without pairs, fp32
+// MFMA kernel 374); 56x56 batch 8 10.3 us (14.4); 8 channels at 112x112, batch 4,
+// 15.1 us (32.8). The output's stores are most of what is left.
 template <int R, int S, int NBW, bool POOL, bool PAIR>
 __global__ __launch_bounds__(kDnsMaxThreads) void spconv_dense_kernel(DenseArgs a, const float *__restrict__ xp,
                                                                             const float *__restrict__ wpk,

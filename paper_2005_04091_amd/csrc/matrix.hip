@@ -6,8 +6,8 @@
 // A workgroup owns (image, tile of TH x TW output pixels, M output channels) and
 // takes the input channels in chunks of O octets. For each chunk it holds in LDS
 //  * the tile's input window, every value split into three bf16 parts (split.h),
-//    as [octet][pixel][part][8 channels] (48 bytes per octet and pixel: a read of
-//    16 consecutive pixels at a 48-byte step touches every bank once);
+//    as [octet][pixel][part][8 channels] (48 bytes per octet and pixel: 16 pixels
+//    side by side start in the 16 different 16-byte bank groups);
 //  * the chunk's part of the filter as dense fragments: zeros, and the CSR
 //    entries scattered over them, split the same way.
 // The product then runs over octet-taps (8 channels under one filter tap), four
@@ -76,6 +76,7 @@ struct MatArgs {
 // slots of 16 rows x 16 bytes per (unit, part, quarter), slot s = unit * 12 +
 // part * 4 + quarter at s * 256 bytes; row i sits at position (i + s) & 15 of
 // its slots, so that one row's slots, cleared together, lie in different banks.
+
 // x / d for 0 <= x < 2^31 and d >= 2 (whose reciprocal's shift is 32 or more).
 __device__ __forceinline__ int fast_div_hi(int x, uint32_t magic, int shift) {
     return (int)(__umulhi((uint32_t)x, magic) >> (shift - 32));
@@ -89,7 +90,7 @@ struct MatTask {
 constexpr uint32_t kMatNone = 0xfffffff0u;
 
 // LDS position of staged column x: the columns one output row reads under a tap
-// (every lsx-th) lie side by side, so that 16 pixels' reads touch every bank once.
+// (every lsx-th) lie side by side, as with stride 1.
 __device__ __forceinline__ int column(const MatArgs &a, int x) {
     return a.lsx == 1 ? x : x % a.lsx * a.hw + x / a.lsx;
 }
@@ -203,11 +204,13 @@ __device__ __forceinline__ void mat_sums_fp32(const MatArgs &a, const float *__r
 }
 
 // What bounds it: on a 56x56 layer of stride 2 (64 to 128 channels, batch 32,
-// density 0.2) 44 us, of which the MFMAs take 12; per chunk the staging (the
-// scatter and the input's split, both vector instructions) and two barriers cost
-// as much again as the MFMAs, and a launch about 12 us beside its chunks. The
+// density 0.2) 43 us back to back (48 in a kernel trace), of which the MFMAs take
+// 12; per chunk the staging (the scatter and the input's split, both vector
+// instructions) and two barriers cost as much again as the MFMAs, and a launch
+// about 12 us beside its chunks. 46 % of its LDS cycles are bank conflicts; which of
+// the scatter, the input's stores and the reads make them has not been told apart. The
 // any-stride kernel walks the entries of that layer in 261 us (154 us at density
-// 0.05, 473 us at 0.5; here 41 and 53 us). Reads a block ahead and bank-free
+// 0.05, 473 us at 0.5; here 40 and 50 us). Reads a block ahead and the 48-byte
 // pixel rows took 3 to 5 % each; loads further ahead than one chunk, three tilings
 // of 32 x 112 per wave and entry windows per wave instead of per lane were
 // slower or no faster.

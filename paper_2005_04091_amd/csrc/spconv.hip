@@ -2190,17 +2190,18 @@ double matrix_us(const MatrixPlan &mp) { return 5.0 + 0.5e-3 * mp.time; }
 // padding, that kernel is the faster one at low density (8.7 against 11.6 us on
 // 100x100, batch 8).
 //
-// Stride 1: where the two planners' models say so by a margin. In microseconds
-// the stride-1 kernel takes 7.5 + 0.27 per thousand modelled cycles and the
-// matrix kernel 5 + 0.5 (within about 10 % on 44 layers of 7x7 to 224x224, 32 to
-// 512 channels, batch 1 to 32, 1x1 to 5x5, densities 0.05 to 0.6; smaller planes,
-// not among them, keep the stride-1 kernel). The line so
-// falls near density 0.25 at 14x14 and 28x28 and 0.4 at 56x56 and 224x224 in
+// Stride 1: where the two planners' models say so by a margin (planes smaller than
+// the fitted ones keep the stride-1 kernel). The line so falls near density 0.25 at 14x14 and 28x28 and 0.4 at 56x56 and 224x224 in
 // batches of 32, and near 0.15 where one image leaves most CUs without a stride-1
 // workgroup. Measured, stride-1 kernel (with its stream) and matrix kernel: 28x28,
 // 128 channels, pooled 45 / 54 us at density 0.2, 68 / 57 at 0.35; 56x56, 64
 // channels 67 / 66 at 0.35, 93 / 72 at 0.5; 14x14, 256 channels, one image 15 / 17
-// at 0.05, 31 / 21 at 0.2. `pl` is the stride-1 plan for the padded input without
+// at 0.05, 31 / 21 at 0.2. Kernel times alone: the pad pass that an unpadded input
+// with W not a multiple of 4 costs the stride-1 kernel (2.9 us and more) does not
+// count, since the choice has to be the same for the padded input, which a chained
+// layer or a caller of the C functions has in hand. The stream's side of the model
+// serves calls without one too (their walk decodes the entries and is slower), so
+// that packing a stream for a layer or not follows one rule. `pl` is the stride-1 plan for the padded input without
 // the row hint (whose imbalance factor orders tilings and overstates times), so
 // that the choice, and with it the order of the sums, depends on neither.
 bool use_matrix(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, bool pool, long long nnz,
