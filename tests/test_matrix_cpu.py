@@ -69,3 +69,26 @@ def plan_time(sp):
     t = time.perf_counter()
     plan(sp, 1, 4, 64, 30, 30, 3, 3, 2, 1, 900)
     return time.perf_counter() - t
+
+
+def test_plans_of_many_threads_are_those_of_one(sp):
+    """The remembered choices are shared: eight threads planning more layers than a
+    set holds, in different orders, get what one thread gets."""
+    import threading
+    shapes = [dict(N=1 + i % 3, C=64 + 8 * (i % 5), K=64, H=14 + i % 40, W=14 + i % 40, R=3, S=3, stride=1 + i % 2,
+                   pad=1, nnz=9 * 64 * 20 + i) for i in range(150)]
+    want = [plan(sp, **s) for s in shapes]
+    wrong = []
+
+    def work(t):
+        for j in range(600):
+            i = (j * (2 * t + 1) + 17 * t) % len(shapes)
+            if plan(sp, **shapes[i]) != want[i]:
+                wrong.append(i)
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(8)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
