@@ -291,14 +291,15 @@ int spconv_pack_lowered(int N, int C, int H, int W, const spconv_csr *csr, int K
 
 /* Kernel families reported by spconv_plan. */
 #define SPCONV_KERNEL_STRIDE1 1 /* stride 1: channel-chunked LDS staging, lanes own padded-width pixels */
-#define SPCONV_KERNEL_GENERIC 2 /* any stride, fewer than 8 input channels */
+#define SPCONV_KERNEL_GENERIC 2 /* any stride: what the matrix kernel does not take */
 #define SPCONV_KERNEL_DENSE 3   /* dense filter on the matrix cores (spconv_forward_dense) */
 /* spconv_kernel_variants only: the stride-1 tilings also built to run several
  * work items per workgroup with a lowered stream (the launch takes that form
  * when the plan has more work items than launch_workgroups). */
 #define SPCONV_KERNEL_STRIDE1_TILED 4
 /* CSR filter on the matrix cores, for calls without a lowered stream: strided
- * layers of 8 or more input channels, and stride-1 ones where it is modelled
+ * layers of 8 or more input channels (with a window that fits its LDS and fewer
+ * images than pass 2^32 threads), and stride-1 ones where it is modelled
  * faster than the stride-1 kernel (dense enough filters).
  * Arithmetic of this kernel and of the dense one: fp32 values as three bf16 parts
  * each, six part products to a product, fp32 sums. For inputs and filter values

@@ -31,7 +31,8 @@
 // gather-accumulate, not a dense contraction. Calls without a lowered stream
 // whose filters are dense enough, or whose stride is not 1, run in matrix.hip
 // (use_matrix below states the rule); the any-stride kernel here is left with
-// strided layers of fewer than 8 input channels.
+// strided layers of fewer than 8 input channels and those matrix.hip has no tiling
+// for (windows past the LDS, grids past 2^32 threads).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1532,10 +1533,10 @@ __global__ __launch_bounds__(kS1Threads) __attribute__((amdgpu_waves_per_eu(4, 4
     s1_epilogue<PI, IPW, RPW, POOL>(a, accE, accO, krow, ig, ty, y0, 0, wave, lane, lds, lds, bias, res, out);
 }
 
-// Generic-stride kernel (strided layers of fewer than 8 channels): waves split the pixels of the tile and every wave
-// walks all KT rows; each pixel keeps its own LDS base (y*stride*Wp +
-// x*stride), so a nonzero costs one address add per pixel. Correct for any
-// stride; the stride-1 kernel above is the fast path.
+// Generic-stride kernel (strided layers that matrix.hip does not take): waves
+// split the pixels of the tile and every wave walks all KT rows; each pixel keeps
+// its own LDS base (y*stride*Wp + x*stride), so a nonzero costs one address add
+// per pixel. Correct for any stride; the stride-1 kernel above is the fast path.
 template <int P, int KT, bool POOL>
 __global__ __launch_bounds__(kThreads) void spconv_generic_kernel(FwdArgs a, const float *__restrict__ xp,
                                                                   const int32_t *__restrict__ rowptr,
