@@ -298,6 +298,8 @@ def test_dense_input_without_a_finite_value(sp, value):
         say("dense", value, L.plan(N))
         x = torch.full((N, C, H, W), value)
         out = L.run(x.cuda()).cpu()
+        raw = L.forward(x.cuda(), pad_in_kernel=True).cpu()
+        assert torch.equal(torch.isnan(raw), torch.isnan(out)) and torch.equal(torch.nan_to_num(raw), torch.nan_to_num(out))
         ref = torch.nn.functional.conv2d(x[:1], torch.from_numpy(layer.w), torch.from_numpy(layer.bias), padding=1)
         assert not torch.isfinite(ref).any()
         if pool:  # a window's maximum skips NaN, unless all four are

@@ -278,3 +278,30 @@ def test_small_values(sp, scale, side):
     _, other = oracle.conv(*one, layer.mask, None, 2, 1, False, False)
     lost = 2.0 ** -134 * other if scale < 2.0 ** -109 else 0.0
     assert (np.abs(out.cpu().numpy() - ref) <= 1e-6 * ab + lost).all()
+
+
+@pytest.mark.parametrize("case", STRIDE1)
+def test_stride1_sums_that_are_not_finite(sp, case):
+    """A few infinite and NaN pixels: the unpadded input gives the padded one's bits,
+    and both what the stride-1 kernel gives (which multiplies no zero of the filter)."""
+    import torch
+    N, C, K, H, W, R, d, pool = case
+    layer = synth.random_layer(9700 + H, N, C, K, H, W, R, R, 1, R // 2, d, False, pool, True, False)
+    L, _ = _on_device(sp, layer)
+    x = torch.from_numpy(layer.x).cuda()
+    rng = np.random.default_rng(H)
+    for v in (float("inf"), -float("inf"), float("nan"), 3.4028e38):
+        x[rng.integers(N), rng.integers(C), rng.integers(H), rng.integers(W)] = v
+    x[N - 1, C - 1, H - 1, W - 1] = float("inf")
+    out, raw = L.run(x), L.forward(x)
+    lw = torch.from_numpy(sp.spconv_pack_lowered(L.host_csr, N, H, W, 1, L.pad, L.flags, L.csr.max_row_nnz)).cuda()
+    walked = sp.spconv_forward_ex(L.pad_input(x), N, C, H, W, L.csr, K, R, R, 1, L.pad, L.bias, L.flags, lowered=lw)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.isnan(out), torch.isnan(raw)) and torch.equal(torch.nan_to_num(out), torch.nan_to_num(raw))
+    assert not torch.isfinite(walked).all()
+    assert torch.equal(torch.isnan(out), torch.isnan(walked)) and torch.equal(torch.isinf(out), torch.isinf(walked))
+    inf = torch.isinf(walked)
+    assert torch.equal(out[inf], walked[inf])
+    fin = torch.isfinite(walked) & (walked.abs() < 1e30)
+    # (well within 1e-5 of the sum of |w * x|, up to some 500 products of order 1 here)
+    assert torch.allclose(out[fin], walked[fin], rtol=1e-4, atol=1e-3)
